@@ -11,22 +11,41 @@ namespace lenia {
 // VALU instructions as SGPR operands.
 typedef const __attribute__((address_space(4))) float cfloat;
 
-// Block id -> tile id.  The dispatcher deals workgroups round-robin over the
-// 8 XCDs (block b runs on XCD b & 7), each XCD with its own L2.  Tiles are
-// grouped into runs of kTileRun consecutive tiles and run r goes to XCD r & 7:
-// the tiles of a run share an L2, so their overlapping halos are re-read from
-// it, and every XCD gets runs from all over the tile list, so regions of
-// uneven cost (active creatures, empty space) are spread evenly.  Tiles past
-// the last whole group of 8 runs map to themselves.
-constexpr int kTileRun = 512;
-
+// Block id -> position in the tile order.  The dispatcher deals workgroups
+// round-robin over the 8 XCDs (block b runs on XCD b & 7), each XCD with its
+// own L2.  The order is cut into runs of consecutive tiles and run r goes to
+// XCD r & 7: the tiles of a run share an L2, so their overlapping halos are
+// re-read from it, and every XCD gets runs from all over the order, so regions
+// of uneven cost (active creatures, empty space) are spread evenly.  Runs hold
+// 512 tiles, fewer where that would leave an XCD less than four of them; what
+// does not fill a whole group of 8 runs is cut into 8 contiguous pieces.
 __device__ __forceinline__ int xcd_tile(int bid, int nb)
 {
-    const int full = (nb / (8 * kTileRun)) * (8 * kTileRun);
-    if (bid >= full) return bid;
-    const int xcd = bid & 7, k = bid >> 3;
-    const int run = (k / kTileRun) * 8 + xcd;
-    return run * kTileRun + (k % kTileRun);
+    int lg = 9;
+    while (lg > 4 && nb < (32 << lg)) --lg;
+    const int full = (nb >> (lg + 3)) << (lg + 3);
+    const int xcd = bid & 7;
+    if (bid < full) {
+        const int k = bid >> 3;
+        return ((((k >> lg) << 3) + xcd) << lg) + (k & ((1 << lg) - 1));
+    }
+    const int rem = nb - full, k = (bid - full) >> 3;
+    return full + xcd * (rem >> 3) + min(xcd, rem & 7) + k;
+}
+
+// Position in the tile order -> tile row and column: bands of kBand tile rows,
+// each walked column by column, so that a run of consecutive tiles is a block
+// of the plane (64 tiles: 8 x 8) rather than a part of a row, and both the row
+// and the column halos of a tile are its neighbours' shortly before or after.
+constexpr int kBand = 8;
+
+__device__ __forceinline__ void band_tile(int t, int tiles_x, int n_tiles, int& ty, int& tx)
+{
+    const int per = kBand * tiles_x;
+    const int band = t / per, r = t - band * per;
+    const int rows = min(kBand, n_tiles / tiles_x - band * kBand);
+    tx = r / rows;
+    ty = band * kBand + (r - tx * rows);
 }
 
 __device__ __forceinline__ float clip01(float x) { return fminf(fmaxf(x, 0.f), 1.f); }

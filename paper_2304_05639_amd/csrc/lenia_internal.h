@@ -234,6 +234,11 @@ step_launch_fn find_step_launcher(int table, int R, int ty, int tx);
 // the ring-decomposed kernel form (genes P[9][NK][H][W]); null if not compiled
 step_launch_fn find_ring_step_launcher(int table, int R, int ty, int tx);
 batch_launch_fn find_batch_launcher(int table, int R, int ty, int tx);
+// four cells per lane (lenia_quad.hip): null where (table, R, tile) has no such
+// kernel; worlds must satisfy quad_fits
+step_launch_fn find_quad_step_launcher(int table, int R, int ty, int tx);
+batch_launch_fn find_quad_batch_launcher(int table, int R, int ty, int tx);
+bool quad_fits(int R, int ty, int tx, int H, int W);
 // candidate tiles compiled for (table, R); returns count, fills up to max pairs
 int step_tile_candidates(int table, int R, int* ty, int* tx, int max);
 hipError_t launch_fill_synthetic(float* A, size_t nA, float* P, size_t plane, int nk,

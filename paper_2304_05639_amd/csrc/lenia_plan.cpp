@@ -383,6 +383,27 @@ static void tune_store(const std::string& key, int ty, int tx, double ms)
 
 lenia_status fill_batch_tables(lenia_plan_t p, float* const* A, float* const* P, hipStream_t s);
 
+// The step kernel of a tile: four cells per lane where every world of the plan
+// is at least one tile large, one cell per lane otherwise.
+static bool worlds_fit_quads(lenia_plan_t p, int ty, int tx)
+{
+    for (const WorldPlan& w : p->worlds)
+        if (!quad_fits(p->R, ty, tx, w.H, w.W)) return false;
+    return true;
+}
+
+static step_launch_fn step_launcher(lenia_plan_t p, int ty, int tx)
+{
+    step_launch_fn f = worlds_fit_quads(p, ty, tx) ? find_quad_step_launcher(p->table, p->R, ty, tx) : nullptr;
+    return f ? f : find_step_launcher(p->table, p->R, ty, tx);
+}
+
+static batch_launch_fn batch_launcher(lenia_plan_t p, int ty, int tx)
+{
+    batch_launch_fn f = worlds_fit_quads(p, ty, tx) ? find_quad_batch_launcher(p->table, p->R, ty, tx) : nullptr;
+    return f ? f : find_batch_launcher(p->table, p->R, ty, tx);
+}
+
 static lenia_status autotune(lenia_plan_t p, hipStream_t s)
 {
     int tys[16], txs[16];
@@ -461,10 +482,10 @@ static lenia_status autotune(lenia_plan_t p, hipStream_t s)
             e = hipEventRecord(e0, s);
             for (int it = 0; it < 3 && e == hipSuccess; ++it) {
                 if (!p->batched) {
-                    e = find_step_launcher(p->table, p->R, ty, tx)(single, p->mode, s);
+                    e = step_launcher(p, ty, tx)(single, p->mode, s);
                 } else {
                     BatchList bl{dtab, ditems, n_items};
-                    e = find_batch_launcher(p->table, p->R, ty, tx)(bl, p->mode, s);
+                    e = batch_launcher(p, ty, tx)(bl, p->mode, s);
                 }
             }
             if (e == hipSuccess) e = hipEventRecord(e1, s);
@@ -492,19 +513,15 @@ static lenia_status autotune(lenia_plan_t p, hipStream_t s)
     return LENIA_OK;
 }
 
-// 8 x 32 cells with one cell per thread (the fastest measured tile at 4096^2
-// and the one with the most parallelism for small worlds).
+// 4 x 64 cells where every world holds such a tile (four cells per lane): a
+// row of the tile is two cache lines, so fewer of the lines that a tile's
+// genes are read from and written to are shared with its neighbours.  Smaller
+// worlds and the single-kernel table: 8 x 32.
 static void default_tile(lenia_plan_t p)
 {
-    int tys[16], txs[16];
-    const int nc = std::min(16, step_tile_candidates(p->table, p->R, tys, txs, 16));
-    p->tile_y = tys[0];
-    p->tile_x = txs[0];
-    for (int i = 0; i < nc; ++i)
-        if (tys[i] == 8 && txs[i] == 32) {
-            p->tile_y = 8;
-            p->tile_x = 32;
-        }
+    const bool wide = find_quad_step_launcher(p->table, p->R, 4, 64) && worlds_fit_quads(p, 4, 64);
+    p->tile_y = wide ? 4 : 8;
+    p->tile_x = wide ? 64 : 32;
 }
 
 static lenia_status finish_tile_choice(lenia_plan_t p, const lenia_desc* d, hipStream_t s)
@@ -526,8 +543,8 @@ static lenia_status finish_tile_choice(lenia_plan_t p, const lenia_desc* d, hipS
         default_tile(p);
     }
     if (st != LENIA_OK) return st;
-    p->step_fn = find_step_launcher(p->table, p->R, p->tile_y, p->tile_x);
-    p->batch_fn = find_batch_launcher(p->table, p->R, p->tile_y, p->tile_x);
+    p->step_fn = step_launcher(p, p->tile_y, p->tile_x);
+    p->batch_fn = batch_launcher(p, p->tile_y, p->tile_x);
     if (!p->step_fn) return set_error(LENIA_ERR_UNSUPPORTED, "tile not compiled in");
     return LENIA_OK;
 }

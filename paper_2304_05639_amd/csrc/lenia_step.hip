@@ -976,6 +976,7 @@ static const Entry kEntries[] = {
     LENIA_ENTRY(Table3x15, TABLE_3x15, 12, 4, 64),
     LENIA_ENTRY(Table3x15, TABLE_3x15, 13, 16, 32),
     LENIA_ENTRY(Table3x15, TABLE_3x15, 13, 8, 32),
+    LENIA_ENTRY(Table3x15, TABLE_3x15, 13, 4, 64),
     LENIA_ENTRY(Table1x1, TABLE_1x1, 13, 16, 32),
     LENIA_ENTRY(Table1x1, TABLE_1x1, 13, 8, 32),
     LENIA_ENTRY(Table1x1, TABLE_1x1, 12, 16, 32),

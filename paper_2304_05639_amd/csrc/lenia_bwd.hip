@@ -26,28 +26,9 @@
 #include "lenia_device.h"
 #include "lenia_internal.h"
 #include "lenia_plan.h"
+#include "lenia_bwd.h"
 
 namespace lenia {
-
-struct BwdArgs {
-    const float* A;          // A_t    [C][H][W]
-    const float* P;          // P_t    [3NK][H][W]
-    const float* U;          // saved potentials [NK][H][W]
-    const uint8_t* alpha;    // saved alpha [H][W]
-    const float* gA1;        // gA_next [C][H][W]
-    const float* gP1;        // gP_next [3NK][H][W] or null (zero)
-    float* gA;               // gA_t (written by the cell pass, completed by the gather pass)
-    float* gP;               // gP_t
-    float* ubar;             // workspace [NK][H][W]
-    float* numbar;           // workspace [3NK][H][W] (gene update only)
-    float* part;             // workspace [n_tiles][NK][3]
-    const float* wt;         // orbit weights [NO][C][8] in the step kernel's orbit order
-    const float* bt;         // shell-height coefficients [NO][C][16] (slot j, shell i at
-                             // j * 3 + i) in the same orbit order
-    int H, W, tiles_x, n_tiles;
-    float dt, eps;
-    int mode;
-};
 
 // ---------------------------------------------------------------------------
 // 1. per-cell pass
@@ -785,7 +766,21 @@ static lenia_status bwd_enqueue(lenia_plan_t p, const float* A_t, const float* P
     a.dt = (float)w.dt;
     a.eps = eps_below(w.eps);
     a.mode = w.mode;
-    hipError_t e = fn(a, w.d_nshells, gbeta, s);
+    a.shc = w.d_shc;
+    a.bcomb = w.d_bcomb;
+    a.n_shells = w.d_nshells;
+    hipError_t e;
+    if (w.mode == MODE_LOCAL_UPDATE && p->table == TABLE_3x15 && quad_fits(p->R, 4, 64, w.H, w.W)) {
+        // the per-tile partials go into the ubar workspace, which this form does
+        // not use (15 floats per cell; a tile needs 45 and holds at least 64 cells
+        // of its own in all but its last row and column)
+        a.tiles_x = (w.W + 63) / 64;
+        a.n_tiles = a.tiles_x * ((w.H + 3) / 4);
+        a.part = ubar;
+        e = launch_bwd_quad(p->R, a, gbeta, s);
+    } else {
+        e = fn(a, w.d_nshells, gbeta, s);
+    }
     if (e != hipSuccess) return hip_fail(e, "adjoint launch");
     return LENIA_OK;
 }

@@ -275,6 +275,38 @@ static lenia_status build_world(lenia_plan_t p, const lenia_desc* d, WorldPlan& 
         hipError_t e0 = hipMemcpyAsync(w.d_shc, keep_c, hsc.size() * sizeof(float), hipMemcpyHostToDevice, s);
         if (e0 != hipSuccess) return hip_fail(e0, "uploading kernel tables");
     }
+    // the adjoint in quads: with M_j = <ubar_k, core_{B,j} (x) A_src>, the shell-
+    // height gradient is sum_j bcomb[i][j] M_j, bcomb = (delta_ij - |S_i| beta_j
+    // / z) / z.  |S_i| and z from the compiled (float) cores, so that a constant
+    // added to A cancels.
+    if (p->table == TABLE_3x15 && (w.R == 12 || w.R == 13)) {
+        std::vector<double> hc((size_t)w.NK * 9, 0.0);
+        for (int k = 0; k < w.NK; ++k) {
+            const int B = w.n_shells[k];
+            const double* beta = &w.beta[3 * k];
+            double size[3] = {0, 0, 0};
+            for (int o = 0; o < NO; ++o)
+                for (int i = 0; i < B; ++i)
+                    if ((w.R == 12 ? ShellBasis<12>::tab.pair[o][B - 1] : ShellBasis<13>::tab.pair[o][B - 1]) ==
+                        shell_pair(B, i)) {
+                        const int a = w.R == 12 ? ShellBasis<12>::tab.a[o] : ShellBasis<13>::tab.a[o];
+                        const int b = w.R == 12 ? ShellBasis<12>::tab.b[o] : ShellBasis<13>::tab.b[o];
+                        const float c = w.R == 12 ? ShellBasis<12>::tab.core[o][B - 1] : ShellBasis<13>::tab.core[o][B - 1];
+                        size[i] += orbit_size(a, b) * (double)c;
+                    }
+            double z = 0.0;
+            for (int i = 0; i < B; ++i) z += beta[i] * size[i];
+            for (int i = 0; i < B; ++i)
+                for (int j = 0; j < B; ++j)
+                    hc[(size_t)k * 9 + i * 3 + j] = ((i == j ? 1.0 : 0.0) - size[i] * beta[j] / z) / z;
+        }
+        if ((st = dmalloc(p, (void**)&w.d_bcomb, hc.size() * sizeof(double))) != LENIA_OK) return st;
+        char* keep_d = new char[hc.size() * sizeof(double)];
+        std::memcpy(keep_d, hc.data(), hc.size() * sizeof(double));
+        host_keep.push_back(keep_d);
+        hipError_t e0 = hipMemcpyAsync(w.d_bcomb, keep_d, hc.size() * sizeof(double), hipMemcpyHostToDevice, s);
+        if (e0 != hipSuccess) return hip_fail(e0, "uploading kernel tables");
+    }
     // shell-height coefficients in the same orbit order: [orbit][source][16],
     // slot j and shell i at j * 3 + i
     std::vector<float> hbt((size_t)NO * w.C * 16, 0.f);

@@ -50,6 +50,7 @@ struct WorldPlan {
     float* d_bcoef = nullptr;      // [NK][3][n_orbits] beta-gradient coefficients
     float* d_bt = nullptr;         // the same in the step kernel's orbit order
     int* d_nshells = nullptr;      // [NK]
+    double* d_bcomb = nullptr;     // [NK][3][3] shell-height combinations (15-kernel table)
     void* dft_f1t = nullptr;       // DFT forms: transform matrices (hi / lo parts),
     void* dft_f2 = nullptr;        //   kernel spectra and the potentials workspace
     void* dft_f3 = nullptr;

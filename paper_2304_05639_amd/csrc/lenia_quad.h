@@ -1,0 +1,83 @@
+// Quads (four cells adjacent in a row, one lane) on gfx950: 16-byte plane
+// accesses, five-point disks with the neighbouring lanes' cells, and the lattice
+// helpers of the kernels that walk a kernel's support in quads.
+#pragma once
+
+#include <type_traits>
+
+#include "lenia_device.h"
+#include "lenia_internal.h"
+
+namespace lenia {
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f4 pld4(plane_t r, uint32_t off)
+{
+    return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+}
+__device__ __forceinline__ void pst4(plane_t r, uint32_t off, f4 v)
+{
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), r, (int)off, 0, 0);
+}
+// non-temporal, as pst_stream
+__device__ __forceinline__ void pst4_stream(plane_t r, uint32_t off, f4 v)
+{
+    typedef unsigned u4 __attribute__((ext_vector_type(4)));
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), r, (int)off, 0, 2);
+}
+
+// f(integral_constant<int, B>), ..., f(integral_constant<int, E - 1>)
+template <int B, int E, class F>
+__device__ __forceinline__ void static_for(F&& f)
+{
+    if constexpr (B < E) {
+        f(std::integral_constant<int, B>{});
+        static_for<B + 1, E>(static_cast<F&&>(f));
+    }
+}
+
+// Largest b with a^2 + b^2 < R^2.
+constexpr int half_width(int R, int a)
+{
+    int w = 0;
+    while ((w + 1) * (w + 1) + a * a < R * R) ++w;
+    return w;
+}
+
+// Index of the orbit of (a, b) in ShellBasis<R>::tab.
+template <int R>
+constexpr int orbit_index(int a, int b)
+{
+    const int hi = a > b ? a : b, lo = a > b ? b : a;
+    for (int o = 0; o < ShellBasis<R>::NO; ++o)
+        if (ShellBasis<R>::tab.a[o] == hi && ShellBasis<R>::tab.b[o] == lo) return o;
+    return -1;
+}
+
+// A quad's five-point disks of one gene plane: the quad, the quads above and
+// below, and for the first and last quad of a tile row the cell beside it (the
+// others take theirs from the neighbouring lane).
+struct QuadDisk {
+    f4 u, c, d;
+    float e;
+};
+
+// Data-parallel primitive controls: the value of the lane before or after
+// within a row of 16 lanes.  A lane whose source is outside its row, or not
+// active, keeps the old value.
+constexpr int kLaneBefore = 0x111, kLaneAfter = 0x101;   // row_shr:1, row_shl:1
+
+// src of the lane before (or after); e in the lanes that begin (or end) a tile
+// row of QR quads.  The neighbouring lane must be active.
+template <int QR, int CTRL>
+__device__ __forceinline__ float beside(float src, float e, bool edge)
+{
+    static_assert(QR == 8 || QR == 16, "a row of 16 lanes holds whole tile rows");
+    const float v = __builtin_bit_cast(
+        float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, e), __builtin_bit_cast(int, src), CTRL, 0xf, 0xf, false));
+    return (QR == 16) ? v : (edge ? e : v);
+}
+
+}  // namespace lenia

@@ -148,50 +148,6 @@ struct BwdTile {
     static constexpr int NQ = PY * QX, IT = (NQ + 63) / 64;
 };
 
-// The walk of one plane staged at c (the quad's cells at floats 12 .. 15 of row
-// c): rows a = 0 .. R - 1 as V_a[x] = row(a)[x] + row(-a)[x], then
-// t = V_a[x + b] + V_a[x - b] per column distance b, handed to use(a, b, t) where
-// wanted(a, b).
-template <int R, int PITCH, class WANTED, class USE>
-__device__ __forceinline__ void walk_quad(const float* c, WANTED wanted, USE use)
-{
-    static_for<0, R>([&](auto ac) {
-        constexpr int a = decltype(ac)::value, w = half_width(R, a);
-        constexpr unsigned need = [] {   // 16-byte groups of the row in use
-            unsigned m = 0;
-            for (int b = (a == 0) ? 1 : 0; b <= w; ++b)
-                if (WANTED::test(a, b))
-                    for (int e = 0; e < 4; ++e) m |= (1u << ((12 + e + b) / 4)) | (1u << ((12 + e - b) / 4));
-            return m;
-        }();
-        if constexpr (need != 0) {
-            // one row at a time: left alone, the compiler reads all rows first
-            // and spills them
-            __builtin_amdgcn_sched_barrier(0);
-            float v[28];
-#pragma unroll
-            for (int q = 0; q < 7; ++q) {
-                if (need & (1u << q)) {
-                    f4 x = *reinterpret_cast<const f4*>(c + a * PITCH + 4 * q);
-                    if constexpr (a > 0) x += *reinterpret_cast<const f4*>(c - a * PITCH + 4 * q);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[4 * q + e] = x[e];
-                }
-            }
-            static_for<(a == 0) ? 1 : 0, w + 1>([&](auto bc) {
-                constexpr int b = decltype(bc)::value;
-                if constexpr (WANTED::test(a, b)) {
-                    float t[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) t[e] = (b == 0) ? v[12 + e] : v[12 + e + b] + v[12 + e - b];
-                    use(ac, bc, t);
-                }
-            });
-        }
-        (void)wanted;
-    });
-}
-
 // Offsets with a nonzero core in shell pair P of B shells.
 template <int R, int B, int P>
 struct InShell {
@@ -201,10 +157,6 @@ struct InShell {
         return ShellBasis<R>::tab.pair[o][B - 1] == P && ShellBasis<R>::tab.core[o][B - 1] != 0.f;
     }
 };
-struct Everywhere {
-    static constexpr bool test(int, int) { return true; }
-};
-
 // Sum over the wave, in lane 63 (a fixed order: within rows of 16 lanes, then
 // across them).
 template <int CTRL, int ROWS>

@@ -239,6 +239,10 @@ batch_launch_fn find_batch_launcher(int table, int R, int ty, int tx);
 step_launch_fn find_quad_step_launcher(int table, int R, int ty, int tx);
 batch_launch_fn find_quad_batch_launcher(int table, int R, int ty, int tx);
 bool quad_fits(int R, int ty, int tx, int H, int W);
+// single-kernel table, global genes, on 4 x 64 tiles (lenia_global.hip); worlds
+// must satisfy quad_fits(R, 4, 64, H, W)
+step_launch_fn find_global_step_launcher(int R);
+batch_launch_fn find_global_batch_launcher(int R);
 // candidate tiles compiled for (table, R); returns count, fills up to max pairs
 int step_tile_candidates(int table, int R, int* ty, int* tx, int max);
 hipError_t launch_fill_synthetic(float* A, size_t nA, float* P, size_t plane, int nk,

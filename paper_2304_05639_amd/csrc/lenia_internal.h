@@ -239,6 +239,8 @@ batch_launch_fn find_batch_launcher(int table, int R, int ty, int tx);
 step_launch_fn find_quad_step_launcher(int table, int R, int ty, int tx);
 batch_launch_fn find_quad_batch_launcher(int table, int R, int ty, int tx);
 bool quad_fits(int R, int ty, int tx, int H, int W);
+// the ring form in quads on 4 x 64 tiles (lenia_ring_quad.hip), as above
+step_launch_fn find_ring_quad_launcher(int table, int R);
 // single-kernel table, global genes, on 4 x 64 tiles (lenia_global.hip); worlds
 // must satisfy quad_fits(R, 4, 64, H, W)
 step_launch_fn find_global_step_launcher(int R);

@@ -566,6 +566,11 @@ static lenia_status finish_tile_choice(lenia_plan_t p, const lenia_desc* d, hipS
         p->run_x = p->tile_x;
         p->step_fn = find_ring_step_launcher(p->table, p->R, p->tile_y, p->tile_x);
         if (!p->step_fn) return set_error(LENIA_ERR_UNSUPPORTED, "ring form not compiled in");
+        if (find_ring_quad_launcher(p->table, p->R) && worlds_fit_quads(p, 4, 64)) {
+            p->run_y = 4;
+            p->run_x = 64;
+            p->step_fn = find_ring_quad_launcher(p->table, p->R);
+        }
         return LENIA_OK;
     }
     if (d->tile_y) {

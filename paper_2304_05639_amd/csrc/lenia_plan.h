@@ -101,7 +101,7 @@ struct lenia_plan_ {
     bool rings = false;            // ring-decomposed kernels (n_ring > 0)
     int tile_y = 0, tile_x = 0;    // as asked for or chosen
     int run_y = 0, run_x = 0;      // tile of the kernel that runs (the same, except for the
-                                   // global-gene step, whose one form serves every choice)
+                                   // global-gene and ring steps, whose quad forms have one tile)
     lenia::step_launch_fn step_fn = nullptr;
     lenia::batch_launch_fn batch_fn = nullptr;
     size_t ws_bytes = 0;

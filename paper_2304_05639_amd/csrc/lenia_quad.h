@@ -80,6 +80,62 @@ __device__ __forceinline__ float beside(float src, float e, bool edge)
     return (QR == 16) ? v : (edge ? e : v);
 }
 
+// Diffusion of the quad (diffuse_disk for each cell, the sums in its order);
+// n[e] = count of values above the cutoff (0: no quotient, d[e] is not used).
+template <int QR>
+__device__ __forceinline__ void diffuse_quad(const QuadDisk& v, bool first, bool last, float cs, float ncs,
+                                             float (&d)[4], float (&n)[4])
+{
+    const float row[6] = {beside<QR, kLaneBefore>(v.c[3], v.e, first), v.c[0], v.c[1], v.c[2], v.c[3],
+                          beside<QR, kLaneAfter>(v.c[0], v.e, last)};
+    float k[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) k[i] = clip01(fmaf(row[i], cs, ncs));
+    const float k12 = k[1] + k[2], k34 = k[3] + k[4];
+    const float h[4] = {k[0] + k12, k12 + k[3], k[2] + k34, k34 + k[5]};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        n[e] = h[e] + (clip01(fmaf(v.u[e], cs, ncs)) + clip01(fmaf(v.d[e], cs, ncs)));
+        const float num = (((v.u[e] + row[e]) + row[e + 1]) + row[e + 2]) + v.d[e];
+        d[e] = clip01(num * __builtin_amdgcn_rcpf(n[e]));
+    }
+}
+
+// Nibble i of a table packed into one integer.
+__device__ __forceinline__ int nibble(uint32_t t, int i) { return (int)((t >> (4 * i)) & 15u); }
+
+// The kernels writing channel c, in summation order, and their positions
+// source * KPS + slot, packed.
+template <class T>
+constexpr uint32_t pack_kernels(int c)
+{
+    uint32_t t = 0;
+    for (int j = 0; j < T::KPD; ++j) t |= (uint32_t)T::kdst[c][j] << (4 * j);
+    return t;
+}
+// The kernels reading channel s, packed.
+template <class T>
+constexpr uint32_t pack_sources(int s)
+{
+    uint32_t t = 0;
+    for (int j = 0; j < T::KPS; ++j) t |= (uint32_t)T::kidx[s][j] << (4 * j);
+    return t;
+}
+template <class T>
+constexpr int position_of(int k)
+{
+    for (int p = 0; p < T::NK; ++p)
+        if (T::kidx[p / T::KPS][p % T::KPS] == k) return p;
+    return -1;
+}
+template <class T>
+constexpr uint32_t pack_positions(int c)
+{
+    uint32_t t = 0;
+    for (int j = 0; j < T::KPD; ++j) t |= (uint32_t)position_of<T>(T::kdst[c][j]) << (4 * j);
+    return t;
+}
+
 // The walk of one plane staged at c (the quad's cells at floats 12 .. 15 of row
 // c): rows a = 0 .. R - 1 as V_a[x] = row(a)[x] + row(-a)[x], then
 // t = V_a[x + b] + V_a[x - b] per column distance b, handed to use(a, b, t) where

@@ -17,12 +17,14 @@ typedef const __attribute__((address_space(4))) float cfloat;
 // XCD r & 7: the tiles of a run share an L2, so their overlapping halos are
 // re-read from it, and every XCD gets runs from all over the order, so regions
 // of uneven cost (active creatures, empty space) are spread evenly.  Runs hold
-// 512 tiles, fewer where that would leave an XCD less than four of them; what
-// does not fill a whole group of 8 runs is cut into 8 contiguous pieces.
+// 512 tiles, fewer where that would leave an XCD without one (four runs an XCD
+// instead of one: 102 against 100 us a step at 1024^2, 152 against 140 for eight
+// steps of 256^2); what does not fill a whole group of 8 runs is cut into 8
+// contiguous pieces.
 __device__ __forceinline__ int xcd_tile(int bid, int nb)
 {
     int lg = 9;
-    while (lg > 4 && nb < (32 << lg)) --lg;
+    while (lg > 4 && nb < (8 << lg)) --lg;
     const int full = (nb >> (lg + 3)) << (lg + 3);
     const int xcd = bid & 7;
     if (bid < full) {
@@ -34,10 +36,11 @@ __device__ __forceinline__ int xcd_tile(int bid, int nb)
 }
 
 // Position in the tile order -> tile row and column: bands of kBand tile rows,
-// each walked column by column, so that a run of consecutive tiles is a block
-// of the plane (64 tiles: 8 x 8) rather than a part of a row, and both the row
-// and the column halos of a tile are its neighbours' shortly before or after.
-constexpr int kBand = 8;
+// each walked column by column.  The row halos of a tile come back from L2 when
+// the next tile row is not far behind: with bands of 8 rows four steps of 1024^2
+// take 542 us, of 2048^2 2010 and of 4096^2 7490, with bands of 4 536, 1918 and
+// 7830, of 2 528, 1877 and 7480, with plain row-major order 528, 1900 and 7750.
+constexpr int kBand = 2;
 
 __device__ __forceinline__ void band_tile(int t, int tiles_x, int n_tiles, int& ty, int& tx)
 {

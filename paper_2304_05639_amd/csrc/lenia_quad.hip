@@ -13,16 +13,16 @@
 // lane a row of the disk is seven 16-byte reads of one channel for all four,
 // 141 reads where the four cells took 1748, and the gene disks of a plane are
 // three 16-byte reads and, in the lanes at the ends of a tile row, one scalar
-// instead of twenty scalars.  The potentials take 0.72 ms (VALU issue) and the
-// dense step 1.74, of which 1.60 remain when the potentials are left out: it
-// is bound by memory traffic (7.4 GB, 4.2 TB/s, where a plain copy of the 45
-// planes in the same plane-by-plane pattern reaches 4.6 to 5.3).  Three
-// threads per quad leave each lane the registers of one channel only (four
-// waves per SIMD) and give small worlds three times the waves.
-// The 4 x 64 tile: with 8 x 32 (one cache line per row) the step takes 1.96
-// ms, with 8 x 64 2.05, 16 x 64 2.00; on a 1021 x 771 world, where every row
-// segment ends in partial lines, 4 x 64 takes 104 us, 8 x 32 145.  The row of
-// 16 quads also reads LDS without bank conflicts.
+// instead of twenty scalars.  The potentials take 0.83 ms (VALU issue) and the
+// dense step 1.87: it is bound by memory traffic (7.4 GB, 4.0 TB/s, where a
+// plain copy of the 45 planes in the same plane-by-plane pattern reaches 4.6 to
+// 5.3).  Three threads per quad leave each lane the registers of one channel
+// only (167 VGPRs, three waves per SIMD; a budget of four waves, which forms
+// more of the walk's sums twice, takes 1.96 ms) and give small worlds three
+// times the waves: 256^2 takes 17 us a step instead of 21, 512^2 36 instead of
+// 48, 1021 x 771 117 instead of 141.  The 4 x 64 tile: a row of 16 quads reads
+// LDS without bank conflicts, and a world's odd right edge cuts the fewest
+// cache lines; 8 x 32 (one line per row) takes 2.0 ms.
 //
 // Tiles at the right and bottom edges are moved up to end at the edge; the
 // cells two tiles share are computed by both, alike, and written twice with
@@ -210,6 +210,7 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
     const int g = (int)threadIdx.x - ch * G;
     const int ly = g / (TX / 4), lq = g % (TX / 4);
     const int gy = y0 + ly, gx = x0 + 4 * lq;
+    const bool lines = (W & 31) == 0;
     float* own = sA + ch * L::REGION;
 
     // 1. stage the channel: the tile and HALO cells around it, wrapped on the
@@ -319,7 +320,7 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
             if (!zero) {
 #pragma unroll
                 for (int i = 0; i < NPG / T::C; ++i)
-                    pst4_stream(plane(wd.P_out + (size_t)(ch * (NPG / T::C) + i) * HW, pb), ob, z);
+                    pst4_rows(lines, plane(wd.P_out + (size_t)(ch * (NPG / T::C) + i) * HW, pb), ob, z);
             }
             if (ch == 0) {
                 const uint32_t none = 0;
@@ -432,7 +433,7 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
                         f4 x;
 #pragma unroll
                         for (int e = 0; e < 4; ++e) x[e] = (dm[e] > eps) ? gene[p][e] : 0.f;
-                        pst4_stream(plane(wd.P_out + (size_t)(p * NK + k) * HW, pb), ob, x);
+                        pst4_rows(lines, plane(wd.P_out + (size_t)(p * NK + k) * HW, pb), ob, x);
                     }
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
@@ -457,7 +458,7 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
                 for (int t = 0; t < 3 * KPS; ++t) {
                     const plane_t pl = plane(wd.P_out + (size_t)((t % 3) * NK + nibble(kpack, t / 3)) * HW, pb);
                     if (whole) {
-                        pst4_stream(pl, ob, f4{0.f, 0.f, 0.f, 0.f});
+                        pst4_rows(lines, pl, ob, f4{0.f, 0.f, 0.f, 0.f});
                     } else {
 #pragma unroll
                         for (int e = 0; e < 4; ++e)

@@ -7,7 +7,7 @@
 // waves serves a 4 x 64 tile, wave s the kernels reading channel s: a lane holds
 // the 21 ring sums of one channel for the four cells of its quad, and a gene
 // plane's disks are three 16-byte reads and, at the ends of a tile row, a scalar:
-// 378 us (three waves per SIMD; 433 with two), 700 x 333 143 -> 102.
+// 353 us (three waves per SIMD; 433 with two), 700 x 333 143 -> 102.
 // The waves meet once, to join alpha and to sum the growth of each target channel
 // (handed over through LDS, added in the order of the one-cell form).
 #include "lenia_device.h"

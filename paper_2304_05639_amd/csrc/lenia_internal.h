@@ -239,6 +239,8 @@ batch_launch_fn find_batch_launcher(int table, int R, int ty, int tx);
 step_launch_fn find_quad_step_launcher(int table, int R, int ty, int tx);
 batch_launch_fn find_quad_batch_launcher(int table, int R, int ty, int tx);
 bool quad_fits(int R, int ty, int tx, int H, int W);
+// a step of the 15-kernel table from given potentials U[NK][H][W], H >= 4, W >= 64
+hipError_t launch_quad_given(const WorldArgs& w, const float* U, int mode, hipStream_t s);
 // the ring form in quads on 4 x 64 tiles (lenia_ring_quad.hip), as above
 step_launch_fn find_ring_quad_launcher(int table, int R);
 // single-kernel table, global genes, on 4 x 64 tiles (lenia_global.hip); worlds

@@ -21,6 +21,11 @@ __device__ __forceinline__ void pst4(plane_t r, uint32_t off, f4 v)
     typedef unsigned u4 __attribute__((ext_vector_type(4)));
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), r, (int)off, 0, 0);
 }
+// non-temporal
+__device__ __forceinline__ f4 pld4_stream(plane_t r, uint32_t off)
+{
+    return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 2));
+}
 // non-temporal, as pst_stream
 __device__ __forceinline__ void pst4_stream(plane_t r, uint32_t off, f4 v)
 {

@@ -192,11 +192,14 @@ __device__ __forceinline__ void quad_potentials(const float* c, cfloat* __restri
     }
 }
 
-template <class T, int R, int TY, int TX, bool FEW>
+// GIVEN: the potentials are read from U (the second kernel of a step whose
+// potentials the MFMA transforms formed).
+template <class T, int R, int TY, int TX, bool FEW, bool GIVEN = false>
 __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mode, float* sA, int* masks, int* flags,
-                                          uint64_t* above_eps)
+                                          uint64_t* above_eps, const float* U = nullptr)
 {
     using L = QuadTile<T, R, TY, TX>;
+    constexpr int REGION = GIVEN ? T::KPS * TY * TX : L::REGION;
     constexpr int NK = T::NK, KPS = T::KPS, G = L::G, NT = L::NT, NPG = 3 * NK;
     constexpr int CELLS = TY * TX;
     static_assert(T::C == 3 && T::KPD == T::KPS, "three channels");
@@ -211,7 +214,7 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
     const int ly = g / (TX / 4), lq = g % (TX / 4);
     const int gy = y0 + ly, gx = x0 + 4 * lq;
     const bool lines = (W & 31) == 0;
-    float* own = sA + ch * L::REGION;
+    float* own = sA + ch * REGION;
 
     // 1. stage the channel: the tile and HALO cells around it, wrapped on the
     // torus.  Lanes take neighbouring columns, four rows (one 16-byte write) at a
@@ -219,10 +222,10 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
     // offset is scalar; the remaining ones are dealt to the lanes by (rows,
     // column).  Rows of a column beyond the halo are not read (their loads fall
     // past the plane and give 0).
-    const bool may_skip = (mode == MODE_LOCAL_UPDATE) && (wd.U_save == nullptr);
+    const bool may_skip = !GIVEN && (mode == MODE_LOCAL_UPDATE) && (wd.U_save == nullptr);
     const bool want_flags = (wd.flags_out != nullptr);
     float most = 0.f;
-    {
+    if constexpr (!GIVEN) {
         constexpr int I0 = L::PAD - L::HALO, I1 = L::PAD + TY + L::HALO;   // rows of a column in use: [I0, I1)
         constexpr int NQ = (I1 + 3) / 4, REST = L::PX - 64, IR = (NQ * REST + 63) / 64;
         constexpr uint32_t NONE = 0xFFFFFFF0u;
@@ -296,11 +299,12 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
         const int bits = (__any(above) ? (1 << ch) : 0) | (__any(live) ? 8 : 0);
         if ((threadIdx.x & 63) == 0) flags[threadIdx.x >> 6] = bits;
     }
-    __syncthreads();
+    if constexpr (!GIVEN) __syncthreads();
     const uint32_t ob = 4u * ((uint32_t)gy * (uint32_t)W + (uint32_t)gx);
     f4 a;
+    if constexpr (GIVEN) a = pld4(plane(wd.A + (size_t)ch * HW, pb), ob);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) a[e] = own[(4 * lq + e + L::HALO) * L::PITCH + L::PAD + ly];
+    for (int e = 0; e < 4 && !GIVEN; ++e) a[e] = own[(4 * lq + e + L::HALO) * L::PITCH + L::PAD + ly];
     const plane_t paout = plane(wd.A_out + (size_t)ch * HW, pb);
     const bool upd = (mode == MODE_LOCAL_UPDATE);
     if (may_skip) {
@@ -357,8 +361,29 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
         q.e = pld(pl, oe);
     };
     // 2. potentials of the kernels reading channel ch, four cells of column cx
-    // from row cy
-    {
+    // from row cy (of the quad, where they are given)
+    if constexpr (GIVEN) {
+        const uint32_t spack = (ch == 0) ? pack_sources<T>(0) : (ch == 1) ? pack_sources<T>(1) : pack_sources<T>(2);
+        f4 u[KPS];
+#pragma unroll
+        for (int j = 0; j < KPS; ++j) {
+            const plane_t pu = plane(U + (size_t)nibble(spack, j) * HW, pb);
+            u[j] = lines ? pld4_stream(pu, ob) : pld4(pu, ob);
+        }
+        bool ok[4] = {true, true, true, true};
+#pragma unroll
+        for (int j = 0; j < KPS; ++j) {
+            *reinterpret_cast<f4*>(own + j * CELLS + 4 * g) = u[j];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ok[e] = ok[e] && (u[j][e] > wd.eps);
+        }
+        // bit g of word e: every potential of the quad's cell e above the cutoff
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint64_t m = __ballot(ok[e]);
+            if (g == 0) above_eps[ch * 4 + e] = m;
+        }
+    } else {
         const int cx = g % TX, cy = 4 * (g / TX);
         float u[KPS][4];
         quad_potentials<T, R, L::PITCH, FEW>(own + (cx + L::HALO) * L::PITCH + cy, (cfloat*)wd.shc + ch * KPS * 8, u);
@@ -394,7 +419,7 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
     // 3. genes, growth and update of the kernels writing channel ch
     auto u_of = [&](int pos) {
         const int s = (pos * 13) >> 6;   // pos / 5 for pos < 15
-        return *reinterpret_cast<const f4*>(sA + s * L::REGION + (pos - s * KPS) * CELLS + 4 * g);
+        return *reinterpret_cast<const f4*>(sA + s * REGION + (pos - s * KPS) * CELLS + 4 * g);
     };
     static_assert(KPS == 5, "pos / 5");
     float sum[4] = {0.f, 0.f, 0.f, 0.f};
@@ -403,8 +428,15 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
         // alpha needs every potential above the cutoff; a quad where none of
         // the four has it reads no genes, unless a quad beside it does (which
         // takes its end cells from this lane)
-        const uint64_t um = above_eps[ly & 3] & above_eps[4 + (ly & 3)] & above_eps[8 + (ly & 3)];
-        const int ualpha = (int)(um >> ((ly >> 2) * TX + 4 * lq)) & 15;
+        int ualpha = 0;
+        if constexpr (GIVEN) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                ualpha |= (int)(((above_eps[e] & above_eps[4 + e] & above_eps[8 + e]) >> g) & 1) << e;
+        } else {
+            const uint64_t um = above_eps[ly & 3] & above_eps[4 + (ly & 3)] & above_eps[8 + (ly & 3)];
+            ualpha = (int)(um >> ((ly >> 2) * TX + 4 * lq)) & 15;
+        }
         const bool reads = (ualpha | __builtin_amdgcn_update_dpp(0, ualpha, kLaneBefore, 0xf, 0xf, false) |
                             __builtin_amdgcn_update_dpp(0, ualpha, kLaneAfter, 0xf, 0xf, false)) != 0;
         float dm[4];   // running minimum of the diffused genes (0: alpha fails)
@@ -543,6 +575,30 @@ __global__ __launch_bounds__((QuadTile<T, R, TY, TX>::NT), 3) void quad_batch_ke
     for (int i = 0; i < NW; ++i) words[i] = src[i];
     const WorldArgs wd = __builtin_bit_cast(WorldArgs, words);
     quad_tile<T, R, TY, TX, false>(wd, tile, mode, sh.sA, sh.masks, sh.flags, sh.above_eps);
+}
+
+// The rest of a step whose potentials are given, bound by memory traffic (111
+// planes; 90 us at 1024^2, 5.2 TB/s, where one cell per lane took 123).  The
+// potentials are not needed again: read past the caches where rows are whole
+// lines (the step with its transforms takes 188 us at 1024^2, 203 read through
+// them; 700 x 333 155 and 151).
+template <class T>
+__global__ __launch_bounds__(192, 4) void quad_given_kernel(WorldArgs wd, const float* U, int mode)
+{
+    constexpr int TY = 4, TX = 64;
+    __shared__ __attribute__((aligned(16))) float sU[T::NK * TY * TX];
+    __shared__ int masks[192];
+    __shared__ uint64_t above_eps[T::C * 4];
+    quad_tile<T, 12, TY, TX, false, true>(wd, xcd_tile(blockIdx.x, gridDim.x), mode, sU, masks, nullptr, above_eps, U);
+}
+
+hipError_t launch_quad_given(const WorldArgs& w, const float* U, int mode, hipStream_t s)
+{
+    WorldArgs a = w;
+    a.tiles_x = (w.W + 63) / 64;
+    a.n_tiles = (w.H + 3) / 4 * a.tiles_x;
+    hipLaunchKernelGGL((quad_given_kernel<Table3x15>), dim3(a.n_tiles), dim3(192), 0, s, a, U, mode);
+    return hipGetLastError();
 }
 
 // At most one workgroup per compute unit: a SIMD then runs one wave, so the

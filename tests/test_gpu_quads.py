@@ -84,3 +84,20 @@ def test_backward(L, oracle, H, W, R):
     g = oracle.step_vjp(oracle.Desc.from_world(w), w.A, w.P, gA1, gP1)
     for got, want, tol in zip(plan.backward(A, P, saved, dev(gA1), dev(gP1)), (g["gA"], g["gP"], g["gbeta"]), (2e-5, 2e-5, 1e-4)):
         assert np.abs(host(got) - want).max() <= tol * np.abs(want).max()
+
+
+@pytest.mark.parametrize("H,W,R", [(4, 64, 12), (5, 65, 12), (25, 63, 12), (51, 131, 13), (40, 96, 12)])
+def test_step_from_given_potentials(L, H, W, R):
+    """The two-kernel step of the transform form (its second kernel in quads
+    where the world holds a 4 x 64 tile) against the one-kernel step, which
+    treats one cell at a time: identical bits, and the saved alpha set exactly
+    where genes remain."""
+    w = inputs.test_world(H, W, seed=900 + H + W, n_blobs=max(1, H * W // 600), R=R)
+    two, one = L.Plan(w, conv=3), L.Plan(w, conv=3, dft_fused=True)
+    for n in (1, 3):
+        a, b = gpu_step(two, w.A, w.P, n_steps=n), gpu_step(one, w.A, w.P, n_steps=n)
+        assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+    saved = two.new_saved().zero_()
+    a = gpu_step(two, w.A, w.P, saved=saved)
+    alpha = host(two.saved_views(saved)[1])
+    assert np.array_equal(alpha != 0, (a[1] > 0).any(axis=(0, 1)))

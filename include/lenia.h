@@ -292,7 +292,7 @@ typedef struct {
  * n_steps iterations of the above.  Buffers as for lenia_step (in place or
  * out of place), except that the wall cells of (A_in, P_in) are zeroed in
  * place first.  events: host array of n_steps entries (may be NULL when both
- * rates are 0).  Workspace of 3 bytes per cell allocated on first use, and the
+ * rates are 0).  Workspace of 2 bytes per cell allocated on first use, and the
  * tile bytes of lenia_step for calls of more than two steps.
  * Ring-decomposed kernels and batched plans: LENIA_ERR_UNSUPPORTED.
  */

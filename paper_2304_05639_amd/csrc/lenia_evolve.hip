@@ -19,8 +19,12 @@ constexpr int kMaxOxy = 16;
 // Wall cells of the state: A and all gene planes set to 0.  Each lane takes
 // kWallCells cells a grid apart, so that consecutive lanes read consecutive
 // mask bytes and write consecutive cells of every plane; all of a lane's mask
-// bytes are read before any store, so their latencies overlap.
-constexpr int kWallCells = 8;
+// bytes are read before any store, so their latencies overlap.  Row y of the grid
+// takes planes y, y + kWallRows, ...: walls cover few cells, so what bounds the
+// kernel is the chain of a lane's stores, one plane after the other, and reading
+// the mask kWallRows times costs less (1024^2, 48 planes: 8 us, 12.7 with eight
+// cells a lane and one row, 11 with eight of each).
+constexpr int kWallCells = 2, kWallRows = 4;
 
 __global__ __launch_bounds__(256) void walls_kernel(float* A, float* P, const uint8_t* walls,
                                                     uint32_t HW, int C, int NPG)
@@ -37,10 +41,32 @@ __global__ __launch_bounds__(256) void walls_kernel(float* A, float* P, const ui
     for (int k = 0; k < kWallCells; ++k) {
         if (!m[k]) continue;
         const uint32_t idx = i0 + (uint32_t)k * stride;
-        for (int c = 0; c < C; ++c) A[(size_t)c * HW + idx] = 0.f;
+        for (int c = blockIdx.y; c < C; c += kWallRows) A[(size_t)c * HW + idx] = 0.f;
         if (P)
-            for (int q = 0; q < NPG; ++q) P[(size_t)q * HW + idx] = 0.f;
+            for (int q = blockIdx.y; q < NPG; q += kWallRows) P[(size_t)q * HW + idx] = 0.f;
     }
+}
+
+// The gene updates of one iteration: mutation of plane mut_plane inside the
+// square, then penalization of pen_plane inside the penalizing area, on the new
+// gene state and only where alpha = 1.  The square's first row and column (sy0,
+// sx0) come reduced to [0, H) x [0, W), so a cell's offsets from them need one
+// conditional add.  An operator that is off adds 0 and touches nothing.
+struct Updates {
+    float* P;
+    const uint8_t* flags;
+    int mut_plane, sy0, sx0, side;
+    float mut_add;
+    int pen_plane;
+    float pen_add;
+};
+
+__device__ __forceinline__ bool mutates(const Updates& u, int y, int x, int H, int W)
+{
+    int oy = y - u.sy0, ox = x - u.sx0;
+    oy += (oy < 0) ? H : 0;
+    ox += (ox < 0) ? W : 0;
+    return u.mut_add != 0.f && oy < u.side && ox < u.side;
 }
 
 // out(x) = 1 if some cell d of the disk |d| <= r around x (on the torus) has
@@ -50,10 +76,15 @@ __global__ __launch_bounds__(256) void walls_kernel(float* A, float* P, const ui
 // rows (lanes are columns): the row's clear cells become two ballots over
 // columns [0, 64) and [64, TX + 2r) (TX = 64, 2r <= 32), and the prefix count
 // at column j is the number of set bits below j, the lane-masked bit count.
+//
+// The second pass (LAST) finds the penalizing area, and as a cell's updates need
+// its own byte of it only, they are made here, in place of writing the area for
+// a kernel of its own to read (1024^2: 12.4 us, where the two took 16.3).
 constexpr int OXY_TY = 16, OXY_TX = 64;
 
+template <bool LAST>
 __global__ __launch_bounds__(256) void disk_clear_kernel(const uint8_t* src, int bit, uint8_t* out,
-                                                         int H, int W, int r)
+                                                         int H, int W, int r, Updates upd)
 {
     constexpr int MR = kMaxOxy;
     constexpr int RY = OXY_TY + 2 * MR, RX = OXY_TX + 2 * MR + 1;
@@ -61,6 +92,18 @@ __global__ __launch_bounds__(256) void disk_clear_kernel(const uint8_t* src, int
     const int tiles_x = (W + OXY_TX - 1) / OXY_TX;
     const int ty0 = (blockIdx.x / tiles_x) * OXY_TY, tx0 = (blockIdx.x % tiles_x) * OXY_TX;
     const int ny = OXY_TY + 2 * r, nx = OXY_TX + 2 * r;
+    // the thread's cells: column lx, rows ly0, ly0 + 4, ...
+    constexpr int NQ = OXY_TY / 4;
+    const int lx = threadIdx.x & 63, ly0 = threadIdx.x >> 6;
+    const size_t HW = (size_t)H * W;
+    uint8_t alive[NQ];
+    if constexpr (LAST) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int gy = ty0 + ly0 + 4 * q, gx = tx0 + lx;
+            alive[q] = (gy < H && gx < W) ? upd.flags[(size_t)gy * W + gx] & 1 : 0;
+        }
+    }
     // stage the tile and its r-cell halo (wrapped): wave v takes rows v, v + 4,
     // ..., all of its loads issued before the first ballot; a single wrap
     // suffices unless the torus is smaller than tile + halo
@@ -100,12 +143,10 @@ __global__ __launch_bounds__(256) void disk_clear_kernel(const uint8_t* src, int
         }
     }
     __syncthreads();
-    // the thread's cells: column lx, rows ly0, ly0 + 4, ..., all tested together
-    // so that the counts of one disk row are read in one round trip; the disk
-    // row dy spans columns [lx - w, lx + w], w the largest with w^2 + dy^2 <= r^2
-    // (uniform, updated as dy runs from -r to r)
-    constexpr int NQ = OXY_TY / 4;
-    const int lx = threadIdx.x & 63, ly0 = threadIdx.x >> 6;
+    // the thread's cells are all tested together so that the counts of one disk
+    // row are read in one round trip; the disk row dy spans columns [lx - w,
+    // lx + w], w the largest with w^2 + dy^2 <= r^2 (uniform, updated as dy runs
+    // from -r to r)
     bool hit[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) hit[q] = false;
@@ -124,32 +165,50 @@ __global__ __launch_bounds__(256) void disk_clear_kernel(const uint8_t* src, int
 #pragma unroll
         for (int q = 0; q < NQ; ++q) hit[q] = hit[q] || (z1[q] != z0[q]);
     }
+    if constexpr (!LAST) {
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        const int gy = ty0 + ly0 + 4 * q, gx = tx0 + lx;
-        if (gy < H && gx < W) out[(size_t)gy * W + gx] = (uint8_t)hit[q];
+        for (int q = 0; q < NQ; ++q) {
+            const int gy = ty0 + ly0 + 4 * q, gx = tx0 + lx;
+            if (gy < H && gx < W) out[(size_t)gy * W + gx] = (uint8_t)hit[q];
+        }
+    } else {
+        // all cells' genes are read before the first store; one plane may take
+        // both updates, the penalization then on top of the mutation
+        const bool same = upd.mut_plane == upd.pen_plane;
+        float* pm = upd.P + (size_t)upd.mut_plane * HW;
+        float* pp = upd.P + (size_t)upd.pen_plane * HW;
+        bool mut[NQ], pen[NQ];
+        float gm[NQ], gp[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int gy = ty0 + ly0 + 4 * q, gx = tx0 + lx;
+            const size_t idx = (size_t)gy * W + gx;
+            mut[q] = alive[q] && mutates(upd, gy, gx, H, W);
+            pen[q] = alive[q] && hit[q] && upd.pen_add != 0.f;
+            gm[q] = mut[q] ? pm[idx] : 0.f;
+            gp[q] = pen[q] ? pp[idx] : 0.f;
+        }
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const size_t idx = (size_t)(ty0 + ly0 + 4 * q) * W + (tx0 + lx);
+            if (mut[q]) {
+                gm[q] += upd.mut_add;
+                if (same) gp[q] = gm[q];
+                pm[idx] = gm[q];
+            }
+            if (pen[q]) pp[idx] = gp[q] + upd.pen_add;
+        }
     }
 }
 
-// Mutation, then penalization, of one iteration, on the new gene state, one
-// thread per cell.  The square's first row and column (sy0, sx0) come reduced
-// to [0, H) x [0, W), so a cell's offsets from them need one conditional add.
-__global__ __launch_bounds__(256) void events_kernel(float* P, const uint8_t* flags,
-                                                     const uint8_t* epen, int H, int W,
-                                                     int mut_plane, int sy0, int sx0, int side,
-                                                     float mut_add, int pen_plane, float pen_add)
+// The mutation alone (no penalization), one thread per cell.
+__global__ __launch_bounds__(256) void mutation_kernel(Updates upd, int H, int W)
 {
     const uint32_t HW = (uint32_t)H * (uint32_t)W;
     const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
-    if (idx >= HW || !(flags[idx] & 1)) return;       // both act only where alpha = 1
-    if (mut_add != 0.f) {
-        const int y = (int)(idx / (uint32_t)W), x = (int)(idx - (uint32_t)y * W);
-        int oy = y - sy0, ox = x - sx0;
-        oy += (oy < 0) ? H : 0;
-        ox += (ox < 0) ? W : 0;
-        if (oy < side && ox < side) P[(size_t)mut_plane * HW + idx] += mut_add;
-    }
-    if (pen_add != 0.f && epen[idx]) P[(size_t)pen_plane * HW + idx] += pen_add;
+    if (idx >= HW || !(upd.flags[idx] & 1)) return;
+    const int y = (int)(idx / (uint32_t)W), x = (int)(idx - (uint32_t)y * W);
+    if (mutates(upd, y, x, H, W)) upd.P[(size_t)upd.mut_plane * HW + idx] += upd.mut_add;
 }
 
 }  // namespace lenia
@@ -209,13 +268,12 @@ extern "C" lenia_status lenia_step_evolve(lenia_plan_t p, float* A_in, float* P_
         }
         if (!p->evo_flags) {
             void* q = nullptr;
-            if (device_alloc(&q, 3 * cells) != hipSuccess)
+            if (device_alloc(&q, 2 * cells) != hipSuccess)
                 return set_error(LENIA_ERR_OUT_OF_MEMORY, "operator workspace");
             p->allocations.push_back(q);
-            p->ws_bytes += 3 * cells;
+            p->ws_bytes += 2 * cells;
             p->evo_flags = (uint8_t*)q;
             p->evo_eoxy = p->evo_flags + cells;
-            p->evo_epen = p->evo_eoxy + cells;
         }
         const size_t abytes = w.a_elems() * sizeof(float), pbytes = w.p_elems() * sizeof(float);
         const unsigned cell_blocks = (unsigned)((cells + 255) / 256);
@@ -224,7 +282,7 @@ extern "C" lenia_status lenia_step_evolve(lenia_plan_t p, float* A_in, float* P_
         hipError_t e = hipSuccess;
         if (n_steps == 0) {
             if (evo->walls)
-                hipLaunchKernelGGL(walls_kernel, dim3(wall_blocks), dim3(256), 0, s, A_in, P_in, evo->walls,
+                hipLaunchKernelGGL(walls_kernel, dim3(wall_blocks, kWallRows), dim3(256), 0, s, A_in, P_in, evo->walls,
                                    (uint32_t)cells, w.C, NPG);
             if (A_out != A_in) e = hipMemcpyAsync(A_out, A_in, abytes, hipMemcpyDeviceToDevice, s);
             if (e == hipSuccess && P_out != P_in) e = hipMemcpyAsync(P_out, P_in, pbytes, hipMemcpyDeviceToDevice, s);
@@ -272,7 +330,7 @@ extern "C" lenia_status lenia_step_evolve(lenia_plan_t p, float* A_in, float* P_
             }
             // 1. walls on the state the step starts from
             if (evo->walls)
-                hipLaunchKernelGGL(walls_kernel, dim3(wall_blocks), dim3(256), 0, s, curA, curP, evo->walls,
+                hipLaunchKernelGGL(walls_kernel, dim3(wall_blocks, kWallRows), dim3(256), 0, s, curA, curP, evo->walls,
                                    (uint32_t)cells, w.C, NPG);
             // 2. the step, with the flags
             a.A = curA;
@@ -288,26 +346,30 @@ extern "C" lenia_status lenia_step_evolve(lenia_plan_t p, float* A_in, float* P_
             }
             if (e != hipSuccess) return hip_fail(e, "step launch");
             // 3. penalizing area, 4-5. gene updates
-            if (pen) {
-                hipLaunchKernelGGL(disk_clear_kernel, dim3(oxy_tiles), dim3(256), 0, s, p->evo_flags, 1,
-                                   p->evo_eoxy, w.H, w.W, evo->r_oxy);
-                hipLaunchKernelGGL(disk_clear_kernel, dim3(oxy_tiles), dim3(256), 0, s, p->evo_eoxy, 0,
-                                   p->evo_epen, w.H, w.W, evo->r_oxy);
-            }
             if (mut || pen) {
                 const lenia_event& ev = events[i - 1];
-                const float mut_add = mut ? (float)(evo->gamma_mut * (double)ev.mut_delta) : 0.f;
-                const float pen_add = pen ? (float)(evo->gamma_pen * (double)ev.pen_delta) : 0.f;
                 // the square's first row and column on the torus
                 const int64_t y0 = ((int64_t)ev.mut_y0 - evo->mut_half) % w.H;
                 const int64_t x0 = ((int64_t)ev.mut_x0 - evo->mut_half) % w.W;
                 // an operator that is off leaves its (unchecked) fields unused
-                const int mut_plane = mut ? ev.mut_p * w.NK + ev.mut_k : 0;
-                const int pen_plane = pen ? ev.pen_p * w.NK + ev.pen_k : 0;
-                hipLaunchKernelGGL(events_kernel, dim3(cell_blocks), dim3(256), 0, s, nP,
-                                   p->evo_flags, p->evo_epen, w.H, w.W, mut_plane,
-                                   (int)(y0 < 0 ? y0 + w.H : y0), (int)(x0 < 0 ? x0 + w.W : x0),
-                                   2 * evo->mut_half, mut_add, pen_plane, pen_add);
+                Updates u;
+                u.P = nP;
+                u.flags = p->evo_flags;
+                u.mut_plane = mut ? ev.mut_p * w.NK + ev.mut_k : 0;
+                u.sy0 = (int)(y0 < 0 ? y0 + w.H : y0);
+                u.sx0 = (int)(x0 < 0 ? x0 + w.W : x0);
+                u.side = 2 * evo->mut_half;
+                u.mut_add = mut ? (float)(evo->gamma_mut * (double)ev.mut_delta) : 0.f;
+                u.pen_plane = pen ? ev.pen_p * w.NK + ev.pen_k : 0;
+                u.pen_add = pen ? (float)(evo->gamma_pen * (double)ev.pen_delta) : 0.f;
+                if (pen) {
+                    hipLaunchKernelGGL((disk_clear_kernel<false>), dim3(oxy_tiles), dim3(256), 0, s,
+                                       p->evo_flags, 1, p->evo_eoxy, w.H, w.W, evo->r_oxy, u);
+                    hipLaunchKernelGGL((disk_clear_kernel<true>), dim3(oxy_tiles), dim3(256), 0, s,
+                                       p->evo_eoxy, 0, (uint8_t*)nullptr, w.H, w.W, evo->r_oxy, u);
+                } else {
+                    hipLaunchKernelGGL(mutation_kernel, dim3(cell_blocks), dim3(256), 0, s, u, w.H, w.W);
+                }
             }
             e = hipGetLastError();
             if (e != hipSuccess) return hip_fail(e, "operator launch");

@@ -121,7 +121,6 @@ struct lenia_plan_ {
     // organic), the oxygenated area and the penalizing area
     uint8_t* evo_flags = nullptr;
     uint8_t* evo_eoxy = nullptr;
-    uint8_t* evo_epen = nullptr;
     // LENIA_FLAG_CHECK_FINITE: one bit per scanned buffer of a call
     bool check_finite = false;
     uint32_t* d_nonfinite = nullptr;

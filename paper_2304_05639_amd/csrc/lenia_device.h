@@ -17,14 +17,14 @@ typedef const __attribute__((address_space(4))) float cfloat;
 // XCD r & 7: the tiles of a run share an L2, so their overlapping halos are
 // re-read from it, and every XCD gets runs from all over the order, so regions
 // of uneven cost (active creatures, empty space) are spread evenly.  Runs hold
-// 512 tiles, fewer where that would leave an XCD without one (four runs an XCD
-// instead of one: 102 against 100 us a step at 1024^2, 152 against 140 for eight
-// steps of 256^2); what does not fill a whole group of 8 runs is cut into 8
-// contiguous pieces.
+// 64 tiles, or 32 where there are fewer than four runs an XCD: with 512, three
+// steps of a sparse 4096^2 world take 4070 us instead of 3950 and eight of 512^2
+// 268 instead of 242, the XCDs finishing unevenly (with 32, 4030 and 242), while
+// dense worlds take the same (4096^2 1.87 ms a step).  What does not fill a whole
+// group of 8 runs is cut into 8 contiguous pieces.
 __device__ __forceinline__ int xcd_tile(int bid, int nb)
 {
-    int lg = 9;
-    while (lg > 4 && nb < (8 << lg)) --lg;
+    const int lg = (nb < (32 << 6)) ? 5 : 6;
     const int full = (nb >> (lg + 3)) << (lg + 3);
     const int xcd = bid & 7;
     if (bid < full) {

@@ -396,7 +396,7 @@ def batched_throughput(steps: int = 500, with_cpu: bool = True):
            "cells": cells, "worlds": len(worlds), "steps": steps, "tile": [info.tile_y, info.tile_x],
            "alive_frac_end": alive_end,
            "roofline": hbm_roofline(BYTES_PER_CELL * cells, ms, "batched", window,
-                                    "step_batch_kernel (autotuned tile)")}
+                                    "quad_batch_kernel (autotuned tile)")}
     if with_cpu:
         from oracle import oracle as O
         i = min(range(len(worlds)), key=lambda j: worlds[j].H)

@@ -99,7 +99,12 @@ typedef struct {
     int32_t r_diff;             /* diffusion disk radius (1)                     */
     int32_t conv;               /* lenia_conv                                    */
     int32_t tile_y, tile_x;     /* output tile of the fused step kernel; 0,0 =
-                                   the autotuned / default choice                */
+                                   the autotuned / default choice.  Ring-
+                                   decomposed kernels, and global genes with one
+                                   kernel, have a 4 x 64 form for worlds of H >=
+                                   R, W >= 64: it is their default there and is
+                                   not autotuned; 8 x 32 (and with one kernel
+                                   16 x 32) asks for the one-cell kernels.       */
     uint32_t flags;             /* LENIA_FLAG_*                                  */
     int32_t n_ring;             /* 0: the ring-shell kernels above (beta, shells);
                                    > 0: ring-decomposed kernels with localized

@@ -291,8 +291,8 @@ extern "C" lenia_status lenia_step_evolve(lenia_plan_t p, float* A_in, float* P_
         }
         const bool inplace = (A_in == A_out);
         WorldArgs a = w.args_template();
-        a.tiles_x = (w.W + p->run_x - 1) / p->run_x;
-        a.n_tiles = ((w.H + p->run_y - 1) / p->run_y) * a.tiles_x;
+        a.tiles_x = (w.W + p->tile_x - 1) / p->tile_x;
+        a.n_tiles = ((w.H + p->tile_y - 1) / p->tile_y) * a.tiles_x;
         a.flags_out = p->evo_flags;
         // zero-gene tile flags of the two output buffers, as in lenia_step (the
         // walls only write zeros and the events only touch cells where alpha

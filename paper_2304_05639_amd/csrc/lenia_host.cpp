@@ -217,6 +217,10 @@ lenia_status validate(const lenia_desc* d)
                     "1->0, 1->2, 2->0, 2->1)");
     if (d->genotype_update && d->r_diff != 1)
         return fail(LENIA_ERR_UNSUPPORTED, "only r_diff = 1 is compiled in");
+    // the 4 x 64 tile of the ring form and of the global-gene step of one kernel,
+    // which a plan reports where the world holds one
+    const bool one_quad_tile = d->tile_y == 4 && d->tile_x == 64 && quad_fits(d->R, 4, 64, d->H, d->W) &&
+                               (rings || (table == TABLE_1x1 && !d->localized));
     if (rings) {
         if (table != TABLE_3x15 || d->R != 12 || d->n_ring != 24)
             return fail(LENIA_ERR_UNSUPPORTED, "ring-decomposed kernels are compiled for 3 channels "
@@ -225,8 +229,9 @@ lenia_status validate(const lenia_desc* d)
             return fail(LENIA_ERR_UNSUPPORTED, "ring-decomposed kernels use the direct form");
         if (d->flags & LENIA_FLAG_AUTOTUNE)
             return fail(LENIA_ERR_UNSUPPORTED, "no autotuning for ring-decomposed kernels");
-        if (d->tile_y && !(d->tile_y == 8 && d->tile_x == 32))
-            return fail(LENIA_ERR_UNSUPPORTED, "ring-decomposed kernels run 8 x 32 tiles");
+        if (d->tile_y && !(d->tile_y == 8 && d->tile_x == 32) && !one_quad_tile)
+            return fail(LENIA_ERR_UNSUPPORTED, "ring-decomposed kernels run 8 x 32 tiles, and 4 x 64 "
+                                               "where the world holds such a tile");
         return LENIA_OK;
     }
     if (d->conv != LENIA_CONV_AUTO && d->conv != LENIA_CONV_DIRECT_F32 &&
@@ -238,7 +243,7 @@ lenia_status validate(const lenia_desc* d)
         return fail(LENIA_ERR_UNSUPPORTED, "no kernel compiled for R = " + std::to_string(d->R) +
                                                " with this table");
     if (d->tile_y) {
-        bool ok = false;
+        bool ok = one_quad_tile;
         for (int i = 0; i < nc && i < 16; ++i) ok |= (tys[i] == d->tile_y && txs[i] == d->tile_x);
         if (!ok) return fail(LENIA_ERR_UNSUPPORTED, "requested tile not compiled in");
     }

@@ -559,18 +559,24 @@ static void default_tile(lenia_plan_t p)
 static lenia_status finish_tile_choice(lenia_plan_t p, const lenia_desc* d, hipStream_t s)
 {
     lenia_status st = LENIA_OK;
+    // The ring form and the global-gene step of one kernel have one quad form, on
+    // 4 x 64 tiles.  It runs unless another tile is asked for (chosen before the
+    // autotuner, whose candidates are the one-cell kernels'); validate() accepts
+    // 4 x 64 for these forms only where it fits.
+    const bool fits = worlds_fit_quads(p, 4, 64) && (!d->tile_y || (d->tile_y == 4 && d->tile_x == 64));
     if (p->rings) {
-        p->tile_y = 8;
-        p->tile_x = 32;
-        p->run_y = p->tile_y;
-        p->run_x = p->tile_x;
-        p->step_fn = find_ring_step_launcher(p->table, p->R, p->tile_y, p->tile_x);
+        const step_launch_fn quad = fits ? find_ring_quad_launcher(p->table, p->R) : nullptr;
+        p->tile_y = quad ? 4 : 8;
+        p->tile_x = quad ? 64 : 32;
+        p->step_fn = quad ? quad : find_ring_step_launcher(p->table, p->R, p->tile_y, p->tile_x);
         if (!p->step_fn) return set_error(LENIA_ERR_UNSUPPORTED, "ring form not compiled in");
-        if (find_ring_quad_launcher(p->table, p->R) && worlds_fit_quads(p, 4, 64)) {
-            p->run_y = 4;
-            p->run_x = 64;
-            p->step_fn = find_ring_quad_launcher(p->table, p->R);
-        }
+        return LENIA_OK;
+    }
+    if (fits && p->table == TABLE_1x1 && p->mode == MODE_GLOBAL && find_global_step_launcher(p->R)) {
+        p->tile_y = 4;
+        p->tile_x = 64;
+        p->step_fn = find_global_step_launcher(p->R);
+        p->batch_fn = find_global_batch_launcher(p->R);
         return LENIA_OK;
     }
     if (d->tile_y) {
@@ -582,15 +588,6 @@ static lenia_status finish_tile_choice(lenia_plan_t p, const lenia_desc* d, hipS
         default_tile(p);
     }
     if (st != LENIA_OK) return st;
-    p->run_y = p->tile_y;
-    p->run_x = p->tile_x;
-    if (p->table == TABLE_1x1 && p->mode == MODE_GLOBAL && find_global_step_launcher(p->R) && worlds_fit_quads(p, 4, 64)) {
-        p->run_y = 4;
-        p->run_x = 64;
-        p->step_fn = find_global_step_launcher(p->R);
-        p->batch_fn = find_global_batch_launcher(p->R);
-        return LENIA_OK;
-    }
     p->step_fn = step_launcher(p, p->tile_y, p->tile_x);
     p->batch_fn = batch_launcher(p, p->tile_y, p->tile_x);
     if (!p->step_fn) return set_error(LENIA_ERR_UNSUPPORTED, "tile not compiled in");
@@ -669,7 +666,7 @@ static lenia_status make_plan(const lenia_desc* ds, int n, void* stream, lenia_p
         std::vector<int2> items;
         for (int i = 0; i < n; ++i) {
             const WorldPlan& w = p->worlds[i];
-            const int nt = tiles_of(w.H, p->run_y) * tiles_of(w.W, p->run_x);
+            const int nt = tiles_of(w.H, p->tile_y) * tiles_of(w.W, p->tile_x);
             for (int t = 0; t < nt; ++t) items.push_back(make_int2(i, t));
         }
         p->n_items = (int)items.size();
@@ -811,8 +808,8 @@ lenia_status lenia_step(lenia_plan_t p, const float* A_in, const float* P_in, fl
         }
         const bool inplace = (A_in == A_out);
         WorldArgs a = w.args_template();
-        a.tiles_x = tiles_of(w.W, p->run_x);
-        a.n_tiles = tiles_of(w.H, p->run_y) * a.tiles_x;
+        a.tiles_x = tiles_of(w.W, p->tile_x);
+        a.n_tiles = tiles_of(w.H, p->tile_y) * a.tiles_x;
         // zero-gene tile flags of the two output buffers: known only for what
         // this call has written, so cleared at its start
         const bool zero_flags = upd && !saved && !conv_is_dft(p->conv) && n_steps > 2;
@@ -909,8 +906,8 @@ lenia_status lenia_potentials(lenia_plan_t p, const float* A, float* U, void* st
             e = launch_dft_potentials(p, w, A, U, s);
         } else {
             WorldArgs a = w.args_template();
-            a.tiles_x = tiles_of(w.W, p->run_x);
-            a.n_tiles = tiles_of(w.H, p->run_y) * a.tiles_x;
+            a.tiles_x = tiles_of(w.W, p->tile_x);
+            a.n_tiles = tiles_of(w.H, p->tile_y) * a.tiles_x;
             a.A = A;
             a.U_save = U;
             e = p->step_fn(a, MODE_POTENTIALS, s);
@@ -937,7 +934,7 @@ lenia_status fill_batch_tables(lenia_plan_t p, float* const* A, float* const* P,
     for (int i = 0; i < n; ++i) {
         const WorldPlan& w = p->worlds[i];
         if (w.mode == MODE_LOCAL_UPDATE)
-            zbytes += 2 * (size_t)tiles_of(w.W, p->run_x) * tiles_of(w.H, p->run_y);
+            zbytes += 2 * (size_t)tiles_of(w.W, p->tile_x) * tiles_of(w.H, p->tile_y);
     }
     if (zbytes && !p->batch_zero) {
         lenia_status zs = dmalloc(p, (void**)&p->batch_zero, zbytes);
@@ -948,8 +945,8 @@ lenia_status fill_batch_tables(lenia_plan_t p, float* const* A, float* const* P,
     for (int i = 0; i < n; ++i) {
         WorldPlan& w = p->worlds[i];
         WorldArgs a = w.args_template();
-        a.tiles_x = tiles_of(w.W, p->run_x);
-        a.n_tiles = tiles_of(w.H, p->run_y) * a.tiles_x;
+        a.tiles_x = tiles_of(w.W, p->tile_x);
+        a.n_tiles = tiles_of(w.H, p->tile_y) * a.tiles_x;
         const bool upd = (w.mode == MODE_LOCAL_UPDATE);
         if (upd && p->batch_zero) {
             a.p_zero = p->batch_zero + zoff;

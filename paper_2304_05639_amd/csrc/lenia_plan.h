@@ -99,9 +99,7 @@ struct lenia_plan_ {
     bool batched = false;
     int table = 0, mode = 0, R = 0, conv = LENIA_CONV_DIRECT_F32;
     bool rings = false;            // ring-decomposed kernels (n_ring > 0)
-    int tile_y = 0, tile_x = 0;    // as asked for or chosen
-    int run_y = 0, run_x = 0;      // tile of the kernel that runs (the same, except for the
-                                   // global-gene and ring steps, whose quad forms have one tile)
+    int tile_y = 0, tile_x = 0;    // tile of the step kernel
     lenia::step_launch_fn step_fn = nullptr;
     lenia::batch_launch_fn batch_fn = nullptr;
     size_t ws_bytes = 0;

@@ -124,7 +124,8 @@ typedef struct {
 } lenia_desc;
 
 #define LENIA_FLAG_AUTOTUNE 1u  /* time the tile candidates at plan time and
-                                   cache the winner per (H, W, R, C, mode)       */
+                                   cache the winner per (sizes of all worlds, R,
+                                   C, mode, version of the step kernels)         */
 #define LENIA_FLAG_CHECK_FINITE 2u
                                 /* debug checks on every call of the plan, before
                                    anything else is enqueued: each caller buffer

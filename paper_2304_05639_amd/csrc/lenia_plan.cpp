@@ -367,17 +367,32 @@ static std::string tune_cache_path()
     return std::string(home ? home : "/tmp") + "/.cache/lenia_mi355x_tune.txt";
 }
 
+// Number of the set of step kernels that a stored choice was timed on, raised when
+// one of them, or the rule that picks one for a tile, changes: choices of another
+// set are not found and are timed again.
+constexpr int kTunedKernels = 2;
+
+// The sizes of all worlds enter (the first four in words, all of them in a hash):
+// which kernel a tile gets depends on the smallest one.
 static std::string tune_key(lenia_plan_t p)
 {
     hipDeviceProp_t prop;
     std::string arch = "gfx?";
     if (hipGetDeviceProperties(&prop, p->device) == hipSuccess) arch = prop.gcnArchName;
     std::ostringstream k;
-    k << arch << ":t" << p->table << ":R" << p->R << ":m" << p->mode << ":"
+    k << arch << ":k" << kTunedKernels << ":t" << p->table << ":R" << p->R << ":m" << p->mode << ":"
       << (p->batched ? "batch" : "single");
-    for (size_t i = 0; i < p->worlds.size() && i < 4; ++i)
-        k << ":" << p->worlds[i].H << "x" << p->worlds[i].W;
-    k << ":n" << p->worlds.size();
+    uint64_t h = 14695981039346656037ull;   // FNV-1a
+    const auto mix = [&h](uint32_t v) {
+        for (int i = 0; i < 4; ++i) h = (h ^ ((v >> (8 * i)) & 255u)) * 1099511628211ull;
+    };
+    for (size_t i = 0; i < p->worlds.size(); ++i) {
+        const WorldPlan& w = p->worlds[i];
+        if (i < 4) k << ":" << w.H << "x" << w.W;
+        mix((uint32_t)w.H);
+        mix((uint32_t)w.W);
+    }
+    k << ":n" << p->worlds.size() << ":s" << std::hex << h;
     return k.str();
 }
 

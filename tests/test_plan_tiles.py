@@ -81,3 +81,29 @@ def test_ring_plan_reports_the_tile_that_runs(H, W, default):
     assert _tile(plan) == _tile(again) == default
     assert all(torch.equal(x, y) for x, y in zip(plan.step(A, P), again.step(A, P)))
     assert _tile(lenia.Plan(w, tile=(8, 32))) == (8, 32)
+
+
+@pytest.mark.gpu
+def test_stored_choices_of_other_kernels_are_not_taken(tmp_path, monkeypatch):
+    """A choice stored under a key that does not name the kernels it was timed on
+    (as earlier versions wrote it) is timed again, and two batches that differ
+    in a later world only do not share one."""
+    import torch
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("LENIA_TUNE_CACHE", str(cache))
+    worlds = [inputs.test_world(64, 64, seed=40 + i, n_blobs=1) for i in range(5)]
+    narrow = inputs.test_world(64, 48, seed=45, n_blobs=1)
+    arch = torch.cuda.get_device_properties(0).gcnArchName
+    # 3-channel table (1), updated genes (mode 2)
+    old = [f"{arch}:t1:R12:m2:single:64x64:n1 16 32 0.001",
+           f"{arch}:t1:R12:m2:batch:64x64:64x64:64x64:64x64:n5 16 32 0.001"]
+    cache.write_text("\n".join(old) + "\n")
+    lenia.Plan(worlds[0], autotune=True)
+    assert len(cache.read_text().splitlines()) == 3
+    for n, batch in enumerate((worlds, worlds[:4] + [narrow])):
+        first = _tile(lenia.BatchedPlan(batch, autotune=True))
+        lines = cache.read_text().splitlines()
+        assert len(lines) == 4 + n                    # timed and stored
+        assert tuple(map(int, lines[-1].split()[1:3])) == first
+        assert _tile(lenia.BatchedPlan(batch, autotune=True)) == first
+        assert len(cache.read_text().splitlines()) == 4 + n   # found

@@ -194,6 +194,49 @@ __device__ __forceinline__ void quad_potentials(const float* c, cfloat* __restri
 
 // GIVEN: the potentials are read from U (the second kernel of a step whose
 // potentials the MFMA transforms formed).
+// Byte offsets of a quad and of its disks' other cells: the rows above and below
+// and, in the lanes at the ends of a tile row, the cell beside it (elsewhere past
+// the plane, no access).
+struct Around {
+    uint32_t u, c, d, e;
+};
+template <int TX>
+__device__ __forceinline__ Around around(int gy, int gx, int lq, int H, int W)
+{
+    const int ym = (gy == 0) ? H - 1 : gy - 1, yp = (gy == H - 1) ? 0 : gy + 1;
+    const uint32_t row = (uint32_t)gy * (uint32_t)W;
+    const bool first = (lq == 0), last = (lq == TX / 4 - 1);
+    int xe = first ? gx - 1 : gx + 4;
+    xe += (xe < 0) ? W : 0;
+    xe -= (xe >= W) ? W : 0;
+    return Around{4u * ((uint32_t)ym * (uint32_t)W + (uint32_t)gx), 4u * (row + (uint32_t)gx),
+                  4u * ((uint32_t)yp * (uint32_t)W + (uint32_t)gx),
+                  (first || last) ? 4u * (row + (uint32_t)xe) : 0xFFFFFFF0u};
+}
+
+// Whether plane 0 of the disks of the tile at (y0, x0) is at or below the cutoff
+// everywhere (alpha then fails in all its cells); if so the channel's A' =
+// clip01(A) is written.  Every wave tests all the tile's cells.
+template <int TY, int TX>
+__device__ __forceinline__ bool still_empty(const WorldArgs& wd, int ch, int y0, int x0)
+{
+    const uint32_t pb = 4u * (uint32_t)wd.H * (uint32_t)wd.W;
+    int lane = (int)threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));   // nothing here is kept for the live tile's code
+    const int lq = lane % (TX / 4);
+    const Around n = around<TX>(y0 + lane / (TX / 4), x0 + 4 * lq, lq, wd.H, wd.W);
+    const plane_t p0 = plane(wd.P, pb);
+    const f4 u = pld4(p0, n.u), c = pld4(p0, n.c), d = pld4(p0, n.d);
+    const float b = pld(p0, n.e);
+    const f4 a = pld4(plane(wd.A + (size_t)ch * wd.H * wd.W, pb), n.c);
+    bool live = n.e != 0xFFFFFFF0u && b > wd.eps;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) live = live || u[e] > wd.eps || c[e] > wd.eps || d[e] > wd.eps;
+    if (__any(live)) return false;
+    pst4(plane(wd.A_out + (size_t)ch * wd.H * wd.W, pb), n.c, f4{clip01(a[0]), clip01(a[1]), clip01(a[2]), clip01(a[3])});
+    return true;
+}
+
 template <class T, int R, int TY, int TX, bool FEW, bool GIVEN = false>
 __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mode, float* sA, int* masks, int* flags,
                                           uint64_t* above_eps, const float* U = nullptr)
@@ -202,28 +245,46 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
     constexpr int REGION = GIVEN ? T::KPS * TY * TX : L::REGION;
     constexpr int NK = T::NK, KPS = T::KPS, G = L::G, NT = L::NT, NPG = 3 * NK;
     constexpr int CELLS = TY * TX;
+    constexpr bool EARLY = !FEW && !GIVEN;
     static_assert(T::C == 3 && T::KPD == T::KPS, "three channels");
     const int H = wd.H, W = wd.W;
     const size_t HW = (size_t)H * W;
     const uint32_t pb = 4u * (uint32_t)HW;
+    const bool may_skip = !GIVEN && (mode == MODE_LOCAL_UPDATE) && (wd.U_save == nullptr);
+    const bool want_flags = (wd.flags_out != nullptr);
+    const bool listed = may_skip && wd.p_zero != nullptr;
+    // (0 without a list: past the end of a plane of 0 bytes)
+    const int zero_byte = EARLY ? (int)__builtin_amdgcn_raw_buffer_load_b8(
+                                      plane((const float*)wd.p_zero, listed ? (uint32_t)wd.n_tiles : 0u), tile, 0, 0)
+                                : 0;
     int tyi, txi;
     band_tile(tile, wd.tiles_x, wd.n_tiles, tyi, txi);
     const int y0 = min(tyi * TY, H - TY), x0 = min(txi * TX, W - TX);
     const int ch = __builtin_amdgcn_readfirstlane((int)threadIdx.x / G);   // wave-uniform
-    const int g = (int)threadIdx.x - ch * G;
-    const int ly = g / (TX / 4), lq = g % (TX / 4);
-    const int gy = y0 + ly, gx = x0 + 4 * lq;
+    const int g0 = (int)threadIdx.x - ch * G;
+    const int ly0 = g0 / (TX / 4), lq0 = g0 % (TX / 4);
+    const int gy = y0 + ly0, gx = x0 + 4 * lq0;
     const bool lines = (W & 31) == 0;
     float* own = sA + ch * REGION;
 
+    // A tile whose genes the output buffer already holds as 0 was empty two steps
+    // ago and mostly still is: where plane 0 confirms it, nothing is staged.  The
+    // window of a 4 x 64 tile is 2236 values a channel, and staging it for every
+    // tile took most of a sparse world's step: 60 steps of 4096^2, blobs of 24 x 24
+    // on 9% of the cells, 41.8 ms, 33.9 so (2048^2, 20 steps, 3.92 and 3.40 ms).
+    // Worlds of at most a workgroup per compute unit do not gain by it and would
+    // wait for the byte (256^2, 8 steps: 143 us, 139 without).
+    bool was_zero = false;
+    if constexpr (EARLY) {
+        was_zero = __builtin_amdgcn_readfirstlane(zero_byte) != 0;
+        if (was_zero && !want_flags && still_empty<TY, TX>(wd, ch, y0, x0)) return;
+    }
     // 1. stage the channel: the tile and HALO cells around it, wrapped on the
     // torus.  Lanes take neighbouring columns, four rows (one 16-byte write) at a
     // time.  The tile's first 64 columns have one row per load, so a row's
     // offset is scalar; the remaining ones are dealt to the lanes by (rows,
     // column).  Rows of a column beyond the halo are not read (their loads fall
     // past the plane and give 0).
-    const bool may_skip = !GIVEN && (mode == MODE_LOCAL_UPDATE) && (wd.U_save == nullptr);
-    const bool want_flags = (wd.flags_out != nullptr);
     float most = 0.f;
     if constexpr (!GIVEN) {
         constexpr int I0 = L::PAD - L::HALO, I1 = L::PAD + TY + L::HALO;   // rows of a column in use: [I0, I1)
@@ -243,7 +304,7 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
             return 4u * (uint32_t)sy * (uint32_t)W;
         };
         f4 v[NQ], r[IR > 0 ? IR : 1];
-        const uint32_t oc = (REST >= 0 || g < L::PX) ? column(g) : NONE;
+        const uint32_t oc = (REST >= 0 || g0 < L::PX) ? column(g0) : NONE;
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
 #pragma unroll
@@ -254,7 +315,7 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
         if constexpr (REST > 0) {
 #pragma unroll
             for (int it = 0; it < IR; ++it) {
-                const int i = g + 64 * it, q = i / REST, xx = 64 + i - q * REST;
+                const int i = g0 + 64 * it, q = i / REST, xx = 64 + i - q * REST;
                 const uint32_t o = column(xx);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -265,13 +326,13 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
         }
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            if (REST >= 0 || g < L::PX) *reinterpret_cast<f4*>(own + g * L::PITCH + 4 * q) = v[q];
+            if (REST >= 0 || g0 < L::PX) *reinterpret_cast<f4*>(own + g0 * L::PITCH + 4 * q) = v[q];
             most = fmaxf(fmaxf(most, fmaxf(v[q][0], v[q][1])), fmaxf(v[q][2], v[q][3]));
         }
         if constexpr (REST > 0) {
 #pragma unroll
             for (int it = 0; it < IR; ++it) {
-                const int i = g + 64 * it, q = i / REST, xx = 64 + i - q * REST;
+                const int i = g0 + 64 * it, q = i / REST, xx = 64 + i - q * REST;
                 if (i < NQ * REST) *reinterpret_cast<f4*>(own + xx * L::PITCH + 4 * q) = r[it];
                 most = fmaxf(fmaxf(most, fmaxf(r[it][0], r[it][1])), fmaxf(r[it][2], r[it][3]));
             }
@@ -300,11 +361,11 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
         if ((threadIdx.x & 63) == 0) flags[threadIdx.x >> 6] = bits;
     }
     if constexpr (!GIVEN) __syncthreads();
-    const uint32_t ob = 4u * ((uint32_t)gy * (uint32_t)W + (uint32_t)gx);
+    const uint32_t ob0 = 4u * ((uint32_t)gy * (uint32_t)W + (uint32_t)gx);
     f4 a;
-    if constexpr (GIVEN) a = pld4(plane(wd.A + (size_t)ch * HW, pb), ob);
+    if constexpr (GIVEN) a = pld4(plane(wd.A + (size_t)ch * HW, pb), ob0);
 #pragma unroll
-    for (int e = 0; e < 4 && !GIVEN; ++e) a[e] = own[(4 * lq + e + L::HALO) * L::PITCH + L::PAD + ly];
+    for (int e = 0; e < 4 && !GIVEN; ++e) a[e] = own[(4 * lq0 + e + L::HALO) * L::PITCH + L::PAD + ly0];
     const plane_t paout = plane(wd.A_out + (size_t)ch * HW, pb);
     const bool upd = (mode == MODE_LOCAL_UPDATE);
     if (may_skip) {
@@ -312,54 +373,33 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
 #pragma unroll
         for (int i = 0; i < NT / 64; ++i) bits |= flags[i];
         const bool dead = want_flags ? (bits & 7) == 0 : (bits & 15) != 15;
-        const bool zero = dead && wd.p_zero != nullptr && wd.p_zero[tile] != 0;
-        if (wd.p_zero != nullptr) {
-            __syncthreads();   // every thread has read the byte
+        if (listed) {
+            if constexpr (!EARLY) {
+                if (dead) {
+                    was_zero = wd.p_zero[tile] != 0;
+                    __syncthreads();   // every thread has read the byte
+                }
+            }
             if (threadIdx.x == 0) wd.p_zero[tile] = dead ? 1 : 0;
         }
         if (dead) {
             // A' = clip01(A), P' = 0 (left alone where the output holds 0 already)
             const f4 z = {0.f, 0.f, 0.f, 0.f};
-            pst4(paout, ob, f4{clip01(a[0]), clip01(a[1]), clip01(a[2]), clip01(a[3])});
-            if (!zero) {
+            pst4(paout, ob0, f4{clip01(a[0]), clip01(a[1]), clip01(a[2]), clip01(a[3])});
+            if (!was_zero) {
 #pragma unroll
                 for (int i = 0; i < NPG / T::C; ++i)
-                    pst4_rows(lines, plane(wd.P_out + (size_t)(ch * (NPG / T::C) + i) * HW, pb), ob, z);
+                    pst4_rows(lines, plane(wd.P_out + (size_t)(ch * (NPG / T::C) + i) * HW, pb), ob0, z);
             }
             if (ch == 0) {
                 const uint32_t none = 0;
-                if (wd.alpha_save) __builtin_memcpy(wd.alpha_save + (ob >> 2), &none, 4);
-                if (wd.flags_out) __builtin_memcpy(wd.flags_out + (ob >> 2), &none, 4);
+                if (wd.alpha_save) __builtin_memcpy(wd.alpha_save + (ob0 >> 2), &none, 4);
+                if (wd.flags_out) __builtin_memcpy(wd.flags_out + (ob0 >> 2), &none, 4);
             }
             return;
         }
     }
 
-    // The gene planes of the kernels writing channel ch, kernel by kernel (m, s,
-    // h): three rows of the quad and, in the lanes at the ends of a tile row, the
-    // cell beside it (past the plane, no access, elsewhere).  AHEAD planes' reads
-    // are in flight ahead of the one being reduced.
-    const uint32_t kpack = (ch == 0) ? pack_kernels<T>(0) : (ch == 1) ? pack_kernels<T>(1) : pack_kernels<T>(2);
-    const uint32_t ppack = (ch == 0) ? pack_positions<T>(0) : (ch == 1) ? pack_positions<T>(1) : pack_positions<T>(2);
-    constexpr int NPL = 3 * KPS, AHEAD = FEW ? 4 : 2, NB = AHEAD + 1;
-    const bool first = (lq == 0), last = (lq == TX / 4 - 1);
-    const int ym = (gy == 0) ? H - 1 : gy - 1, yp = (gy == H - 1) ? 0 : gy + 1;
-    const uint32_t ou = 4u * ((uint32_t)ym * (uint32_t)W + (uint32_t)gx);
-    const uint32_t od = 4u * ((uint32_t)yp * (uint32_t)W + (uint32_t)gx);
-    const uint32_t orow = ob - 4u * (uint32_t)gx;
-    int xe = first ? gx - 1 : gx + 4;
-    xe += (xe < 0) ? W : 0;
-    xe -= (xe >= W) ? W : 0;
-    const uint32_t oe = (first || last) ? orow + 4u * (uint32_t)xe : 0xFFFFFFF0u;
-    QuadDisk v[NB];
-    auto load = [&](int t) {
-        const plane_t pl = plane(wd.P + (size_t)((t % 3) * NK + nibble(kpack, t / 3)) * HW, pb);
-        QuadDisk& q = v[t % NB];
-        q.u = pld4(pl, ou);
-        q.c = pld4(pl, ob);
-        q.d = pld4(pl, od);
-        q.e = pld(pl, oe);
-    };
     // 2. potentials of the kernels reading channel ch, four cells of column cx
     // from row cy (of the quad, where they are given)
     if constexpr (GIVEN) {
@@ -368,12 +408,12 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
 #pragma unroll
         for (int j = 0; j < KPS; ++j) {
             const plane_t pu = plane(U + (size_t)nibble(spack, j) * HW, pb);
-            u[j] = lines ? pld4_stream(pu, ob) : pld4(pu, ob);
+            u[j] = lines ? pld4_stream(pu, ob0) : pld4(pu, ob0);
         }
         bool ok[4] = {true, true, true, true};
 #pragma unroll
         for (int j = 0; j < KPS; ++j) {
-            *reinterpret_cast<f4*>(own + j * CELLS + 4 * g) = u[j];
+            *reinterpret_cast<f4*>(own + j * CELLS + 4 * g0) = u[j];
 #pragma unroll
             for (int e = 0; e < 4; ++e) ok[e] = ok[e] && (u[j][e] > wd.eps);
         }
@@ -381,10 +421,10 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const uint64_t m = __ballot(ok[e]);
-            if (g == 0) above_eps[ch * 4 + e] = m;
+            if (g0 == 0) above_eps[ch * 4 + e] = m;
         }
     } else {
-        const int cx = g % TX, cy = 4 * (g / TX);
+        const int cx = g0 % TX, cy = 4 * (g0 / TX);
         float u[KPS][4];
         quad_potentials<T, R, L::PITCH, FEW>(own + (cx + L::HALO) * L::PITCH + cy, (cfloat*)wd.shc + ch * KPS * 8, u);
         if (wd.U_save) {
@@ -411,12 +451,34 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
 #pragma unroll
             for (int j = 0; j < KPS; ++j) ok = ok && (u[j][e] > wd.eps);
             const uint64_t m = __ballot(ok);
-            if (g == 0) above_eps[ch * 4 + e] = m;
+            if (g0 == 0) above_eps[ch * 4 + e] = m;
         }
     }
     __syncthreads();
 
     // 3. genes, growth and update of the kernels writing channel ch
+    // The gene planes of the kernels writing channel ch, kernel by kernel (m, s,
+    // h), AHEAD planes' reads in flight ahead of the one being reduced.
+    const uint32_t kpack = (ch == 0) ? pack_kernels<T>(0) : (ch == 1) ? pack_kernels<T>(1) : pack_kernels<T>(2);
+    const uint32_t ppack = (ch == 0) ? pack_positions<T>(0) : (ch == 1) ? pack_positions<T>(1) : pack_positions<T>(2);
+    constexpr int NPL = 3 * KPS, AHEAD = FEW ? 4 : 2, NB = AHEAD + 1;
+    // the quad's place is formed again: kept over the walk it takes registers that
+    // the walk holds its reads ahead in (256^2 18.9 us a step instead of 16.9)
+    int tid = (int)threadIdx.x;
+    if constexpr (EARLY) asm volatile("" : "+v"(tid));
+    const int g = tid - ch * G, ly = g / (TX / 4), lq = g % (TX / 4);
+    const bool first = (lq == 0), last = (lq == TX / 4 - 1);
+    const Around at = around<TX>(y0 + ly, x0 + 4 * lq, lq, H, W);
+    const uint32_t ob = at.c;
+    QuadDisk v[NB];
+    auto load = [&](int t) {
+        const plane_t pl = plane(wd.P + (size_t)((t % 3) * NK + nibble(kpack, t / 3)) * HW, pb);
+        QuadDisk& q = v[t % NB];
+        q.u = pld4(pl, at.u);
+        q.c = pld4(pl, ob);
+        q.d = pld4(pl, at.d);
+        q.e = pld(pl, at.e);
+    };
     auto u_of = [&](int pos) {
         const int s = (pos * 13) >> 6;   // pos / 5 for pos < 15
         return *reinterpret_cast<const f4*>(sA + s * REGION + (pos - s * KPS) * CELLS + 4 * g);

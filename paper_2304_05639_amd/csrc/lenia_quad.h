@@ -119,6 +119,49 @@ __device__ __forceinline__ void diffuse_quad(const QuadDisk& v, bool first, bool
     }
 }
 
+// Byte offsets of a quad and of its disks' other cells: the rows above and below
+// and, in the lanes at the ends of a tile row, the cell beside it (elsewhere past
+// the plane, no access).
+struct Around {
+    uint32_t u, c, d, e;
+};
+template <int TX>
+__device__ __forceinline__ Around around(int gy, int gx, int lq, int H, int W)
+{
+    const int ym = (gy == 0) ? H - 1 : gy - 1, yp = (gy == H - 1) ? 0 : gy + 1;
+    const uint32_t row = (uint32_t)gy * (uint32_t)W;
+    const bool first = (lq == 0), last = (lq == TX / 4 - 1);
+    int xe = first ? gx - 1 : gx + 4;
+    xe += (xe < 0) ? W : 0;
+    xe -= (xe >= W) ? W : 0;
+    return Around{4u * ((uint32_t)ym * (uint32_t)W + (uint32_t)gx), 4u * (row + (uint32_t)gx),
+                  4u * ((uint32_t)yp * (uint32_t)W + (uint32_t)gx),
+                  (first || last) ? 4u * (row + (uint32_t)xe) : 0xFFFFFFF0u};
+}
+
+// Whether plane 0 of the disks of the tile at (y0, x0) is at or below the cutoff
+// everywhere (alpha then fails in all its cells); if so the channel's A' =
+// clip01(A) is written.  Every wave tests all the tile's cells.
+template <int TY, int TX>
+__device__ __forceinline__ bool still_empty(const WorldArgs& wd, int ch, int y0, int x0)
+{
+    const uint32_t pb = 4u * (uint32_t)wd.H * (uint32_t)wd.W;
+    int lane = (int)threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));   // nothing here is kept for the live tile's code
+    const int lq = lane % (TX / 4);
+    const Around n = around<TX>(y0 + lane / (TX / 4), x0 + 4 * lq, lq, wd.H, wd.W);
+    const plane_t p0 = plane(wd.P, pb);
+    const f4 u = pld4(p0, n.u), c = pld4(p0, n.c), d = pld4(p0, n.d);
+    const float b = pld(p0, n.e);
+    const f4 a = pld4(plane(wd.A + (size_t)ch * wd.H * wd.W, pb), n.c);
+    bool live = n.e != 0xFFFFFFF0u && b > wd.eps;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) live = live || u[e] > wd.eps || c[e] > wd.eps || d[e] > wd.eps;
+    if (__any(live)) return false;
+    pst4(plane(wd.A_out + (size_t)ch * wd.H * wd.W, pb), n.c, f4{clip01(a[0]), clip01(a[1]), clip01(a[2]), clip01(a[3])});
+    return true;
+}
+
 // Nibble i of a table packed into one integer.
 __device__ __forceinline__ int nibble(uint32_t t, int i) { return (int)((t >> (4 * i)) & 15u); }
 

@@ -39,6 +39,9 @@ __global__ __launch_bounds__(192, 3) void ring_quad_kernel(WorldArgs wd)
     const size_t HW = (size_t)H * W;
     const uint32_t pb = 4u * (uint32_t)HW;
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
+    // (0 without a list: past the end of a plane of 0 bytes)
+    const int zero_byte = (int)__builtin_amdgcn_raw_buffer_load_b8(
+        plane((const float*)wd.p_zero, wd.p_zero != nullptr ? (uint32_t)wd.n_tiles : 0u), tile, 0, 0);
     int tyi, txi;
     band_tile(tile, wd.tiles_x, wd.n_tiles, tyi, txi);
     // tiles at the far edges end there; cells that two tiles share are computed by
@@ -48,6 +51,11 @@ __global__ __launch_bounds__(192, 3) void ring_quad_kernel(WorldArgs wd)
     const int ly = g >> 4, lq = g & 15, gy = y0 + ly, gx = x0 + 4 * lq;
     const uint32_t ob = 4u * ((uint32_t)gy * (uint32_t)W + (uint32_t)gx);
     float* own = sA[ch];
+
+    // a tile that the output buffer holds as 0, as in quad_tile (1024^2, 12 steps
+    // from blobs: 3.15 ms, 3.21 with every tile staged)
+    const bool was_zero = __builtin_amdgcn_readfirstlane(zero_byte) != 0;
+    if (was_zero && still_empty<L::TY, L::TX>(wd, ch, y0, x0)) return;
 
     // 1. stage the channel (rows y0 - HALO .., columns x0 - 12 .., wrapped; a group
     // of four columns across the seam is read cell by cell)
@@ -103,14 +111,11 @@ __global__ __launch_bounds__(192, 3) void ring_quad_kernel(WorldArgs wd)
     const f4 zero4 = {0.f, 0.f, 0.f, 0.f};
     {
         const bool dead = (flags[0] | flags[1] | flags[2]) != 15;
-        const bool zero = dead && wd.p_zero != nullptr && wd.p_zero[tile] != 0;
-        if (wd.p_zero != nullptr) {
-            __syncthreads();   // every thread has read the byte
-            if (threadIdx.x == 0) wd.p_zero[tile] = dead ? 1 : 0;
-        }
+        // (every thread has read the byte before the barrier above)
+        if (wd.p_zero != nullptr && threadIdx.x == 0) wd.p_zero[tile] = dead ? 1 : 0;
         if (dead) {
             pst4(paout, ob, f4{clip01(a[0]), clip01(a[1]), clip01(a[2]), clip01(a[3])});
-            if (!zero) {
+            if (!was_zero) {
 #pragma unroll
                 for (int i = 0; i < NPG / T::C; ++i)
                     pst4_stream(plane(wd.P_out + (size_t)(ch * (NPG / T::C) + i) * HW, pb), ob, zero4);

@@ -40,9 +40,9 @@ def _tiles(H, W, ty, tx):
     return [(min(y, H - ty), min(x, W - tx)) for y in range(0, H, ty) for x in range(0, W, tx)]
 
 
-def _chain(L, w):
-    """The states of STEPS single-step calls of the one-cell kernel."""
-    plan = L.Plan(w, tile=(16, 32))
+def _chain(L, w, tile=(16, 32)):
+    """The states of STEPS single-step calls (of the one-cell kernel)."""
+    plan = L.Plan(w, tile=tile)
     out = [(dev(w.A), dev(w.P))]
     for _ in range(STEPS):
         out.append(plan.step(*out[-1]))
@@ -91,3 +91,25 @@ def test_batch_equals_single_steps(L):
     for w, A, P in zip(worlds, As, Ps):
         a, p = _chain(L, w)[-1]
         assert torch.equal(A, a) and torch.equal(P, p)
+
+
+@pytest.mark.parametrize("H,W", [(97, 161), (40, 64)])
+def test_ring_long_call_equals_single_steps(L, H, W):
+    """(The one-cell ring kernel sums in another order: single steps of the same
+    kernel, which a call of one step runs without the tile list.)"""
+    import torch
+    w = inputs.ring_test_world(H, W, seed=5, n_blobs=0)
+    w.A = np.random.default_rng(H).uniform(0.3, 0.6, (3, H, W)).astype(np.float32)
+    if H > 80:
+        w.P[..., :20, :] = w.P[..., H - 9:, :] = w.P[..., :10] = w.P[..., W - 9:] = 0.0
+    else:
+        w.P[..., 4:20, :] = 0.0
+    states = _chain(L, w, (4, 64))
+    if H > 80:
+        _assert_reaches(states, H, W, 4, 64)
+    plan = L.Plan(w)
+    A, P = dev(w.A), dev(w.P)
+    plan.step(A, torch.where(P > 0, P, 0.3), n_steps=2)
+    A2, P2 = torch.full_like(A, float("nan")), torch.full_like(P, float("nan"))
+    plan.step(A, P, A2, P2, n_steps=STEPS)
+    assert torch.equal(A2, states[-1][0]) and torch.equal(P2, states[-1][1])

@@ -1,6 +1,7 @@
-"""Long calls on worlds that are partly empty: tiles whose genes the call has
+"""Worlds that are partly empty.  In long calls tiles whose genes the call has
 already written as 0 are passed over, come alive when a gene front reaches them,
-and share cells with the tiles moved up at the right and bottom edges."""
+and share cells with the tiles moved up at the right and bottom edges.  Cells
+whose alpha fails on a gene that is read late lose the genes stored before."""
 import numpy as np
 import pytest
 
@@ -113,3 +114,39 @@ def test_ring_long_call_equals_single_steps(L, H, W):
     A2, P2 = torch.full_like(A, float("nan")), torch.full_like(P, float("nan"))
     plan.step(A, P, A2, P2, n_steps=STEPS)
     assert torch.equal(A2, states[-1][0]) and torch.equal(P2, states[-1][1])
+
+
+@pytest.mark.parametrize("H,W,R", [(45, 131, 12), (45, 35, 12), (261, 321, 12), (45, 131, 13)])
+@pytest.mark.parametrize("dft", [False, True])
+def test_genes_that_fail_late(L, oracle, H, W, R, dft):
+    """One gene of one kernel is 0 in single cells (which then diffuse from
+    their neighbours), in crosses, rows and blocks; another kernel's elsewhere.
+    Against the kernel of one cell per lane, and alpha against the oracle's."""
+    import torch
+    if dft and R != 12:
+        pytest.skip("the transform forms are built for R = 12")
+    w = _front_world(H, W, R)
+    rng = np.random.default_rng(3)
+    w.P = np.maximum(w.P, 0.1).astype(np.float32)
+    for p, k in ((2, 14), (2, 2), (1, 11), (0, 9)):
+        gone = rng.random((H, W)) < 0.002
+        gone[rng.integers(H)] = gone[:, rng.integers(W)] = True
+        y, x = rng.integers(H - 9), rng.integers(W - 11)
+        gone[y:y + 9, x:x + 11] = True
+        near = gone.copy()   # disks without any value above the cutoff
+        for dy, dx in ((0, 1), (0, -1), (1, 0), (-1, 0)):
+            near |= np.roll(gone, (dy, dx), (0, 1))
+        w.P[p, k][near] = 0.0
+    a, b = (L.Plan(w, conv=3), L.Plan(w, conv=3, dft_fused=True)) if dft else (L.Plan(w), L.Plan(w, tile=(16, 32)))
+    A, P = dev(w.A), dev(w.P)
+    for n in (1, 3):
+        x, y = a.step(A, P, n_steps=n), b.step(A, P, n_steps=n)
+        assert torch.equal(x[0], y[0]) and torch.equal(x[1], y[1])
+    saved = a.new_saved()
+    _, P1 = a.step(A, P, saved=saved)
+    alpha = a.saved_views(saved)[1].cpu().numpy() != 0
+    r = oracle.step(oracle.Desc.from_world(w), w.A, w.P)
+    sure = (r["amb"] & 1) == 0
+    assert np.array_equal(alpha[sure], (r["alpha"] != 0)[sure])
+    assert 0.02 < (~alpha).mean() < 0.9
+    assert not P1[:, :, torch.tensor(~alpha, device="cuda")].any()

@@ -241,6 +241,9 @@ batch_launch_fn find_quad_batch_launcher(int table, int R, int ty, int tx);
 bool quad_fits(int R, int ty, int tx, int H, int W);
 // a step of the 15-kernel table from given potentials U[NK][H][W], H >= 4, W >= 64
 hipError_t launch_quad_given(const WorldArgs& w, const float* U, int mode, hipStream_t s);
+// the 111 planes of such a step (state, genes in and out, potentials) against the
+// 256 MiB of the last cache
+bool step_exceeds_caches(const WorldArgs& w);
 // the ring form in quads on 4 x 64 tiles (lenia_ring_quad.hip), as above
 step_launch_fn find_ring_quad_launcher(int table, int R);
 // single-kernel table, global genes, on 4 x 64 tiles (lenia_global.hip); worlds

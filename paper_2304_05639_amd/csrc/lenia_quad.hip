@@ -193,8 +193,9 @@ __device__ __forceinline__ void quad_potentials(const float* c, cfloat* __restri
 }
 
 // GIVEN: the potentials are read from U (the second kernel of a step whose
-// potentials the MFMA transforms formed).
-template <class T, int R, int TY, int TX, bool FEW, bool GIVEN = false>
+// potentials the MFMA transforms formed), and it and the genes are written past the
+// caches if STREAM.
+template <class T, int R, int TY, int TX, bool FEW, bool GIVEN = false, bool STREAM = false>
 __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mode, float* sA, int* masks, int* flags,
                                           uint64_t* above_eps, const float* U = nullptr)
 {
@@ -221,7 +222,7 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
     const int g0 = (int)threadIdx.x - ch * G;
     const int ly0 = g0 / (TX / 4), lq0 = g0 % (TX / 4);
     const int gy = y0 + ly0, gx = x0 + 4 * lq0;
-    const bool lines = (W & 31) == 0;
+    const bool lines = GIVEN ? STREAM : (W & 31) == 0;
     float* own = sA + ch * REGION;
 
     // A tile whose genes the output buffer already holds as 0 was empty two steps
@@ -522,7 +523,12 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
 #pragma unroll
                 for (int t = 0; t < 3 * KPS; ++t)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) pst_stream(gene_plane(t), oc[e], 0.f);
+                    for (int e = 0; e < 4; ++e) {
+                        if (GIVEN && !STREAM)
+                            pst(gene_plane(t), oc[e], 0.f);
+                        else
+                            pst_stream(gene_plane(t), oc[e], 0.f);
+                    }
             }
         }
         if (ch == 0 && wd.flags_out) {
@@ -605,25 +611,33 @@ __global__ __launch_bounds__((QuadTile<T, R, TY, TX>::NT), 3) void quad_batch_ke
 
 // The rest of a step whose potentials are given, bound by memory traffic (111
 // planes; 90 us at 1024^2, 5.2 TB/s, where one cell per lane took 123).  The
-// potentials are not needed again: read past the caches where rows are whole
-// lines (the step with its transforms takes 188 us at 1024^2, 203 read through
-// them; 700 x 333 155 and 151).
-template <class T>
+// potentials are not needed again.
+template <class T, bool STREAM>
 __global__ __launch_bounds__(192, 4) void quad_given_kernel(WorldArgs wd, const float* U, int mode)
 {
     constexpr int TY = 4, TX = 64;
     __shared__ __attribute__((aligned(16))) float sU[T::NK * TY * TX];
     __shared__ int masks[192];
     __shared__ uint64_t above_eps[T::C * 4];
-    quad_tile<T, 12, TY, TX, false, true>(wd, xcd_tile(blockIdx.x, gridDim.x), mode, sU, masks, nullptr, above_eps, U);
+    quad_tile<T, 12, TY, TX, false, true, STREAM>(wd, xcd_tile(blockIdx.x, gridDim.x), mode, sU, masks, nullptr, above_eps, U);
 }
 
+bool step_exceeds_caches(const WorldArgs& w) { return 111.0 * 4.0 * w.H * w.W > (double)(256 << 20); }
+
+// Past the caches where the step exceeds them and rows are whole lines (1024^2, the
+// step with its transforms: 208 us, 216 through them), else through them: the next
+// step finds there what this one wrote (four steps of 512^2 302 -> 281 us, of 384^2
+// 273 -> 257, from blobs 271 -> 253; with a kernel of its own each, as either kind
+// of store alone takes 76 registers, a choice between them 125).
 hipError_t launch_quad_given(const WorldArgs& w, const float* U, int mode, hipStream_t s)
 {
     WorldArgs a = w;
     a.tiles_x = (w.W + 63) / 64;
     a.n_tiles = (w.H + 3) / 4 * a.tiles_x;
-    hipLaunchKernelGGL((quad_given_kernel<Table3x15>), dim3(a.n_tiles), dim3(192), 0, s, a, U, mode);
+    if (step_exceeds_caches(w) && w.W % 32 == 0)
+        hipLaunchKernelGGL((quad_given_kernel<Table3x15, true>), dim3(a.n_tiles), dim3(192), 0, s, a, U, mode);
+    else
+        hipLaunchKernelGGL((quad_given_kernel<Table3x15, false>), dim3(a.n_tiles), dim3(192), 0, s, a, U, mode);
     return hipGetLastError();
 }
 

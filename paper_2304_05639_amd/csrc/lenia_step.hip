@@ -845,11 +845,26 @@ __global__ __launch_bounds__(256) void epilogue_kernel(WorldArgs wd, const float
     epilogue_cell<T>(wd, mode, u, a, gy, gx);
 }
 
+// Whether the step from given potentials runs in quads (lenia_quad.hip), on worlds
+// that hold a 4 x 64 tile.  Not below 2^16 cells, where the fifteen planes of a
+// quad's wave, one after the other, take longer than a thread per cell (four steps,
+// transforms included: 96^2 225 against 216 us, 192^2 227 and 221, 256^2 228 and
+// 237).  And not where a step exceeds the caches and 64 consecutive cells are whole
+// 64-byte pieces of a plane but the rows of a tile are not: mostly empty worlds
+// then wait for their zeros to be written, which a thread per cell writes past the
+// caches (four steps of 1000^2 from blobs 838 against 776 us, dense 879 and 911;
+// 1200 x 1210 1149 and 1018, dense 1204 and 1289).
+static bool given_in_quads(const WorldArgs& w)
+{
+    const long cells = w.H * (long)w.W;
+    if (w.H < 4 || w.W < 64 || cells < (1l << 16)) return false;
+    return !step_exceeds_caches(w) || w.W % 32 == 0 || cells % 16 != 0;
+}
+
 template <class T>
 hipError_t launch_epilogue(const WorldArgs& w, const float* U, int mode, hipStream_t s)
 {
-    // in quads where the world holds a 4 x 64 tile (lenia_quad.hip)
-    if (T::NK == 15 && w.H >= 4 && w.W >= 64) return launch_quad_given(w, U, mode, s);
+    if (T::NK == 15 && given_in_quads(w)) return launch_quad_given(w, U, mode, s);
     const unsigned cells = (unsigned)w.H * (unsigned)w.W;
     hipLaunchKernelGGL((epilogue_kernel<T>), dim3((cells + 255) / 256), dim3(256), 0, s, w, U, mode);
     return hipGetLastError();

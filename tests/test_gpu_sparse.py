@@ -123,8 +123,6 @@ def test_genes_that_fail_late(L, oracle, H, W, R, dft):
     their neighbours), in crosses, rows and blocks; another kernel's elsewhere.
     Against the kernel of one cell per lane, and alpha against the oracle's."""
     import torch
-    if dft and R != 12:
-        pytest.skip("the transform forms are built for R = 12")
     w = _front_world(H, W, R)
     rng = np.random.default_rng(3)
     w.P = np.maximum(w.P, 0.1).astype(np.float32)

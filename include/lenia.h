@@ -102,9 +102,11 @@ typedef struct {
                                    the autotuned / default choice.  Ring-
                                    decomposed kernels, and global genes with one
                                    kernel, have a 4 x 64 form for worlds of H >=
-                                   R, W >= 64: it is their default there and is
-                                   not autotuned; 8 x 32 (and with one kernel
-                                   16 x 32) asks for the one-cell kernels.       */
+                                   R, W >= 64: it is their default there (the
+                                   ring form's where it needs no more workgroups
+                                   of a compute unit) and is not autotuned; 8 x 32
+                                   (and with one kernel 16 x 32) asks for the
+                                   one-cell kernels.                             */
     uint32_t flags;             /* LENIA_FLAG_*                                  */
     int32_t n_ring;             /* 0: the ring-shell kernels above (beta, shells);
                                    > 0: ring-decomposed kernels with localized

@@ -571,6 +571,9 @@ static void default_tile(lenia_plan_t p)
     p->tile_x = wide ? 64 : 32;
 }
 
+// Workgroups on the fullest of the 256 compute units.
+static int per_compute_unit(int tiles) { return (tiles + 255) / 256; }
+
 static lenia_status finish_tile_choice(lenia_plan_t p, const lenia_desc* d, hipStream_t s)
 {
     lenia_status st = LENIA_OK;
@@ -580,7 +583,17 @@ static lenia_status finish_tile_choice(lenia_plan_t p, const lenia_desc* d, hipS
     // 4 x 64 for these forms only where it fits.
     const bool fits = worlds_fit_quads(p, 4, 64) && (!d->tile_y || (d->tile_y == 4 && d->tile_x == 64));
     if (p->rings) {
-        const step_launch_fn quad = fits ? find_ring_quad_launcher(p->table, p->R) : nullptr;
+        // A step takes as long as the fullest compute unit.  Where the 4 x 64 tiles,
+        // which cover ragged and narrow worlds less well, need a workgroup more there
+        // than one or two of 8 x 32, one cell per lane is faster (two steps of 577 x 86,
+        // 290 against 219 tiles, 87 us and 109; 300 x 400, 525 against 494, 125 and
+        // 150 from blobs, 126 and 140 dense); with more of them it no longer is
+        // (four against three: 160 to 213 us, 144 to 160 in quads).
+        const WorldPlan& w = p->worlds[0];
+        const int wide = per_compute_unit(tiles_of(w.H, 4) * tiles_of(w.W, 64));
+        const int narrow = per_compute_unit(tiles_of(w.H, 8) * tiles_of(w.W, 32));
+        const bool fuller = !d->tile_y && wide > narrow && narrow <= 2;
+        const step_launch_fn quad = (fits && !fuller) ? find_ring_quad_launcher(p->table, p->R) : nullptr;
         p->tile_y = quad ? 4 : 8;
         p->tile_x = quad ? 64 : 32;
         p->step_fn = quad ? quad : find_ring_step_launcher(p->table, p->R, p->tile_y, p->tile_x);

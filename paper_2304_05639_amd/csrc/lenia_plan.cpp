@@ -588,11 +588,14 @@ static lenia_status finish_tile_choice(lenia_plan_t p, const lenia_desc* d, hipS
         // than one or two of 8 x 32, one cell per lane is faster (two steps of 577 x 86,
         // 290 against 219 tiles, 87 us and 109; 300 x 400, 525 against 494, 125 and
         // 150 from blobs, 126 and 140 dense); with more of them it no longer is
-        // (four against three: 160 to 213 us, 144 to 160 in quads).
+        // (four against three: 160 to 213 us, 144 to 160 in quads), unless there are
+        // a third more tiles (5000 x 80, 2500 against 1875: 376 us and 392, from blobs
+        // 278 and 388; 2400 x 96 224 and 199, from blobs 168 and 187).
         const WorldPlan& w = p->worlds[0];
-        const int wide = per_compute_unit(tiles_of(w.H, 4) * tiles_of(w.W, 64));
-        const int narrow = per_compute_unit(tiles_of(w.H, 8) * tiles_of(w.W, 32));
-        const bool fuller = !d->tile_y && wide > narrow && narrow <= 2;
+        const int wide = tiles_of(w.H, 4) * tiles_of(w.W, 64), narrow = tiles_of(w.H, 8) * tiles_of(w.W, 32);
+        const int fullest = per_compute_unit(wide), fullest_narrow = per_compute_unit(narrow);
+        const bool fuller = !d->tile_y && ((fullest > fullest_narrow && fullest_narrow <= 2) ||
+                                           (fullest > 4 && 4 * wide > 5 * narrow));
         const step_launch_fn quad = (fits && !fuller) ? find_ring_quad_launcher(p->table, p->R) : nullptr;
         p->tile_y = quad ? 4 : 8;
         p->tile_x = quad ? 64 : 32;

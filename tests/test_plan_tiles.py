@@ -71,9 +71,11 @@ def test_global_plan_is_not_autotuned(tmp_path, monkeypatch):
     assert not (tmp_path / "tune.txt").exists()
 
 
-# (290 tiles of 4 x 64 and 219 of 8 x 32, 525 and 494; 256 and 256, 896 and 832)
+# (290 tiles of 4 x 64 and 219 of 8 x 32, 525 and 494, 2500 and 1875; 256 and 256,
+# 896 and 832, 750 and 564)
 @pytest.mark.gpu
-@pytest.mark.parametrize("H,W,default", [(577, 86, (8, 32)), (300, 400, (8, 32)), (256, 256, (4, 64)), (512, 400, (4, 64))])
+@pytest.mark.parametrize("H,W,default", [(577, 86, (8, 32)), (300, 400, (8, 32)), (5000, 80, (8, 32)),
+                                           (256, 256, (4, 64)), (512, 400, (4, 64)), (1500, 70, (4, 64))])
 def test_ring_default_fills_compute_units_evenly(H, W, default):
     w = inputs.ring_test_world(64, 64, seed=1, n_blobs=1)
     w.H, w.W = H, W

@@ -37,7 +37,15 @@ __device__ __forceinline__ void pst4_stream(plane_t r, uint32_t off, f4 v)
 // go past the caches, else through them: there two tiles write parts of one
 // line, which L2 joins (four steps of 1021 x 771: 470 against 498 us, 700^2 258
 // against 279; at 1024^2 the other way round, 558 against 528, and 8200 against
-// 7500 at 4096^2).
+// 7500 at 4096^2).  Rows of whole half lines (W a multiple of 16) go past them on
+// worlds whose 96 planes of a step exceed them by a quarter (from blobs, one step
+// of 1000 x 976 92 us, 104 through them, 1658 x 1232 176 and 213, two dense ones
+// 516 and 533; but 900 x 816 65 and 53, 272 x 400, three steps, 67 and 62).
+__device__ __forceinline__ bool rows_of_lines(int H, int W)
+{
+    constexpr uint32_t kCells = (320u << 20) / (96 * 4);
+    return (W & 31) == 0 || ((W & 15) == 0 && (uint32_t)H * (uint32_t)W > kCells);
+}
 __device__ __forceinline__ void pst4_rows(bool lines, plane_t r, uint32_t off, f4 v)
 {
     if (lines)

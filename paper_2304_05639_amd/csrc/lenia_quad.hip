@@ -222,7 +222,7 @@ __device__ __forceinline__ void quad_tile(const WorldArgs& wd, int tile, int mod
     const int g0 = (int)threadIdx.x - ch * G;
     const int ly0 = g0 / (TX / 4), lq0 = g0 % (TX / 4);
     const int gy = y0 + ly0, gx = x0 + 4 * lq0;
-    const bool lines = GIVEN ? STREAM : (W & 31) == 0;
+    const bool lines = GIVEN ? STREAM : rows_of_lines(H, W);
     float* own = sA + ch * REGION;
 
     // A tile whose genes the output buffer already holds as 0 was empty two steps

@@ -853,15 +853,16 @@ __global__ __launch_bounds__(256) void epilogue_kernel(WorldArgs wd, const float
 // quad's wave, one after the other, take longer than a thread per cell (four steps,
 // transforms included: 96^2 225 against 216 us, 192^2 227 and 221, 256^2 228 and
 // 237).  And not where a step exceeds the caches and 64 consecutive cells are whole
-// 64-byte pieces of a plane but the rows of a tile are not: mostly empty worlds
-// then wait for their zeros to be written, which a thread per cell writes past the
-// caches (four steps of 1000^2 from blobs 838 against 776 us, dense 879 and 911;
-// 1200 x 1210 1149 and 1018, dense 1204 and 1289).
+// lines of a plane but the rows of a tile are not: mostly empty worlds then wait for
+// their zeros to be written, which a thread per cell writes past the caches (four
+// steps of 1000^2 from blobs 842 against 770 us, dense 892 and 908; 1200 x 1210 1152
+// and 1005, dense 1223 and 1285).  Whole half lines are not enough (three steps of
+// 1414 x 520 from blobs 404 against 394, dense 449 and 491).
 static bool given_in_quads(const WorldArgs& w)
 {
     const long cells = w.H * (long)w.W;
     if (w.H < 4 || w.W < 64 || cells < (1l << 16)) return false;
-    return !step_exceeds_caches(w) || w.W % 32 == 0 || cells % 16 != 0;
+    return !step_exceeds_caches(w) || w.W % 32 == 0 || cells % 32 != 0;
 }
 
 template <class T>

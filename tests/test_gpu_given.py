@@ -11,9 +11,10 @@ pytestmark = pytest.mark.gpu
 
 
 # below and from 2^16 cells; from the size whose 111 planes exceed 256 MiB, rows of
-# whole lines, odd rows, and rows that are not whole lines in planes that are
+# whole lines, odd rows, and rows that are not whole lines in planes that are, and in
+# planes of whole half lines
 @pytest.mark.parametrize("H,W", [(1023, 64), (1024, 64), (257, 259), (6000, 100), (787, 768), (788, 768), (779, 779),
-                                 (800, 760), (9700, 64)])
+                                 (800, 760), (804, 756), (9700, 64)])
 def test_two_kernel_step_equals_one_kernel_step(H, W):
     import torch
     from paper_2304_05639_amd import lenia

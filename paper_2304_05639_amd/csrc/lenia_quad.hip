@@ -14,13 +14,13 @@
 // 141 reads where the four cells took 1748, and the gene disks of a plane are
 // three 16-byte reads and, in the lanes at the ends of a tile row, one scalar
 // instead of twenty scalars.  The potentials take 0.83 ms (VALU issue) and the
-// dense step 1.87: it is bound by memory traffic (7.4 GB, 4.0 TB/s, where a
+// dense step 1.84: it is bound by memory traffic (8.0 GB at 4.4 TB/s, where a
 // plain copy of the 45 planes in the same plane-by-plane pattern reaches 4.6 to
 // 5.3).  Three threads per quad leave each lane the registers of one channel
-// only (167 VGPRs, three waves per SIMD; a budget of four waves, which forms
+// only (160 VGPRs, three waves per SIMD; a budget of four waves, which forms
 // more of the walk's sums twice, takes 1.96 ms) and give small worlds three
-// times the waves: 256^2 takes 17 us a step instead of 21, 512^2 36 instead of
-// 48, 1021 x 771 117 instead of 141.  The 4 x 64 tile: a row of 16 quads reads
+// times the waves: 256^2 takes 16.6 us a step instead of 20, 512^2 36 instead of
+// 48, 1021 x 771 117 instead of 159.  The 4 x 64 tile: a row of 16 quads reads
 // LDS without bank conflicts, and a world's odd right edge cuts the fewest
 // cache lines; 8 x 32 (one line per row) takes 2.0 ms.
 //
@@ -62,7 +62,7 @@ struct QuadTile {
 // also gives Q(r, a) for the later orbits (r, a), of which the nearest kHold
 // are held in registers until the walk is at column distance r.  The farther
 // ones are formed again from LDS when they are needed: holding all of them
-// takes 116 registers and leaves two waves per SIMD instead of four.
+// takes 116 registers and leaves two waves per SIMD instead of three.
 template <int R>
 constexpr int kHold = (R == 12) ? 7 : 6;
 
@@ -641,8 +641,10 @@ hipError_t launch_quad_given(const WorldArgs& w, const float* U, int mode, hipSt
     return hipGetLastError();
 }
 
-// At most one workgroup per compute unit: a SIMD then runs one wave, so the
-// kernel may use all its registers (FEW).
+// At most one workgroup per compute unit: a SIMD then runs one wave, and nothing but
+// the wave's own reads ahead hides their latency.  FEW keeps four gene planes in
+// flight instead of two and lets the walk's reads move across its steps (167 VGPRs,
+// within the three waves' budget all the same).
 constexpr int kFewTiles = 256;
 
 template <class T, int R, int TY, int TX>
